@@ -62,6 +62,7 @@ constexpr int kSweepBlock = PS_MF_CELL_THREADS;     // threads per cell workgrou
 constexpr int kTileFloats = PS_MF_CELL_TILE_FLOATS; // LDS sub-tile of a cell (40960: 160 KiB = ts rows of Kp floats)
 static_assert(kSweepBlock % 256 == 0 && kSweepBlock <= 1024, "cell workgroups hold whole 256-thread quarters");
 static_assert(kTileFloats % 512 == 0 && kTileFloats * 4 <= 160 * 1024, "a cell sub-tile holds whole 512-wide rows in LDS");
+constexpr int64_t kPackBytes = 16 << 20;  // packed rows moved per copy where rows are padded (K < Kp)
 constexpr int kLossSegment = 512;  // ratings per lane group of the loss
 // automatic threshold of the dense (MFMA) tiles: ratings per 64 x 64 tile
 #ifndef PS_MF_DENSE_AUTO
@@ -1439,6 +1440,26 @@ __global__ __launch_bounds__(kBlock) void k_seq_commit(SeqCommitArgs a) {
   ring4[a.slot_n * ss4 + r4] = make_float4(rc.x + d.x, rc.y + d.y, rc.z + d.z, rc.w + d.w);
 }
 
+// ------------------------------------------------------------------ factor transfers
+// Rows of K floats packed back to back <-> rows of Kp floats (K < Kp; the padding columns of
+// an unpacked row are written as zeros).  One wavefront per row, lanes over columns.  Bound by
+// the host link that the packed rows cross (a 16 MiB piece takes 0.01 ms here and 0.7 ms
+// there).  The strided host copy that they replace (hipMemcpy2D to or from pageable memory)
+// moved one row at a time, 7 us each.
+__global__ __launch_bounds__(kBlock) void k_pack_rows(const float *__restrict__ rows, int32_t Kp, int64_t n, int32_t K,
+                                                      float *__restrict__ packed) {
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * (kBlock / 64) + threadIdx.x / 64;
+  if (i >= n) return;
+  for (int k = static_cast<int>(threadIdx.x) % 64; k < K; k += 64) packed[i * K + k] = rows[i * Kp + k];
+}
+
+__global__ __launch_bounds__(kBlock) void k_unpack_rows(const float *__restrict__ packed, int32_t K, int64_t n, int32_t Kp,
+                                                        float *__restrict__ rows) {
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * (kBlock / 64) + threadIdx.x / 64;
+  if (i >= n) return;
+  for (int k = static_cast<int>(threadIdx.x) % 64; k < Kp; k += 64) rows[i * Kp + k] = k < K ? packed[i * K + k] : 0.f;
+}
+
 // ------------------------------------------------------------------ kernel dispatch on Kp
 // lane-group shape per padded rank: G lanes x E floats, G <= 16 so that a group sits in
 // one DPP row, E a multiple of 4 for float4 access
@@ -1664,6 +1685,8 @@ struct ps_mf {
   float *ring = nullptr;
   float *partial_u = nullptr, *partial_i = nullptr;
   float *zero_row = nullptr;  // Kp zeros (staging source of empty dense rows)
+  float *pack = nullptr;      // K < Kp: packed rows on their way between the ring and the host
+  int64_t pack_rows = 0;      // rows it holds
   // per-row policies: cached version and ring slot of every user row and (client, item)
   // row, and the staleness profile of the clocks run
   int32_t *ver_u = nullptr, *slot_u = nullptr, *ver_i = nullptr, *slot_i = nullptr;
@@ -2651,6 +2674,11 @@ int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const flo
     return undo(r);
   if ((r = dev_alloc(h, reinterpret_cast<void **>(&h->loss_out), sizeof(double)))) return undo(r);
   if ((r = upload(h, &h->zero_row, std::vector<float>(static_cast<size_t>(h->Kp), 0.f)))) return undo(r);
+  if (h->K != h->Kp) {
+    h->pack_rows = std::min(std::max(h->N, h->M), std::max<int64_t>(1, kPackBytes / (h->K * 4)));
+    if ((r = dev_alloc(h, reinterpret_cast<void **>(&h->pack), static_cast<size_t>(h->pack_rows * h->K) * sizeof(float))))
+      return undo(r);
+  }
   if (per_row_policy(h)) {
     const size_t ni = static_cast<size_t>(h->nclass) * static_cast<size_t>(h->M);
     if ((r = dev_alloc(h, reinterpret_cast<void **>(&h->ver_u), h->N * sizeof(int32_t))) ||
@@ -2681,6 +2709,41 @@ int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const flo
     if ((r = dev_alloc(h, reinterpret_cast<void **>(&h->lwork), static_cast<size_t>(h->N * h->Kp) * sizeof(float))) ||
         (r = dev_alloc(h, reinterpret_cast<void **>(&h->rwork), rw * sizeof(float))))
       return undo(r);
+  }
+  return PS_MF_OK;
+}
+
+// n rows of a factor table between the ring (rows of Kp floats at `rows`) and packed host rows
+// of K floats, in one contiguous copy (K = Kp) or in pieces through the pack buffer.  The
+// handle's stream is idle when it is called, and again when it returns.
+int rows_to_host(ps_mf_t *h, const float *rows, int64_t n, float *host) {
+  if (h->K == h->Kp) {
+    HIP_TRY(h, hipMemcpy(host, rows, static_cast<size_t>(n) * h->K * sizeof(float), hipMemcpyDeviceToHost));
+    return PS_MF_OK;
+  }
+  for (int64_t i = 0; i < n; i += h->pack_rows) {
+    const int64_t m = std::min(h->pack_rows, n - i);
+    hipLaunchKernelGGL(k_pack_rows, dim3(static_cast<unsigned>((m + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock), 0,
+                       h->stream, rows + i * h->Kp, h->Kp, m, h->K, h->pack);
+    HIP_TRY(h, hipGetLastError());
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    HIP_TRY(h, hipMemcpy(host + i * h->K, h->pack, static_cast<size_t>(m) * h->K * sizeof(float), hipMemcpyDeviceToHost));
+  }
+  return PS_MF_OK;
+}
+
+int rows_from_host(ps_mf_t *h, const float *host, int64_t n, float *rows) {
+  if (h->K == h->Kp) {
+    HIP_TRY(h, hipMemcpy(rows, host, static_cast<size_t>(n) * h->K * sizeof(float), hipMemcpyHostToDevice));
+    return PS_MF_OK;
+  }
+  for (int64_t i = 0; i < n; i += h->pack_rows) {
+    const int64_t m = std::min(h->pack_rows, n - i);
+    HIP_TRY(h, hipMemcpy(h->pack, host + i * h->K, static_cast<size_t>(m) * h->K * sizeof(float), hipMemcpyHostToDevice));
+    hipLaunchKernelGGL(k_unpack_rows, dim3(static_cast<unsigned>((m + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock), 0,
+                       h->stream, h->pack, h->K, m, h->Kp, rows + i * h->Kp);
+    HIP_TRY(h, hipGetLastError());
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
   }
   return PS_MF_OK;
 }
@@ -2751,10 +2814,8 @@ int ps_mf_set_factors(ps_mf_t *h, const float *L, const float *R) {
   const size_t slot = static_cast<size_t>((h->N + h->M) * h->Kp);
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   HIP_TRY(h, hipMemset(h->ring, 0, slot * (h->s + 1) * sizeof(float)));
-  HIP_TRY(h, hipMemcpy2D(h->ring, h->Kp * sizeof(float), L, h->K * sizeof(float), h->K * sizeof(float),
-                         static_cast<size_t>(h->N), hipMemcpyHostToDevice));
-  HIP_TRY(h, hipMemcpy2D(h->ring + h->N * h->Kp, h->Kp * sizeof(float), R, h->K * sizeof(float),
-                         h->K * sizeof(float), static_cast<size_t>(h->M), hipMemcpyHostToDevice));
+  HIP_TRY(h, hipDeviceSynchronize());
+  if ((r = rows_from_host(h, L, h->N, h->ring)) || (r = rows_from_host(h, R, h->M, h->ring + h->N * h->Kp))) return r;
   if (per_row_policy(h)) {
     // no row cached yet (version -1); slots 0 keep every address inside the ring
     const size_t ni = static_cast<size_t>(h->nclass) * static_cast<size_t>(h->M);
@@ -2815,11 +2876,8 @@ int ps_mf_get_version(ps_mf_t *h, int64_t v, float *L, float *R) {
   const int64_t slot_stride = (h->N + h->M) * h->Kp;
   const float *base = h->ring + (v % (h->s + 1)) * slot_stride;
   HIP_TRY(h, hipStreamSynchronize(h->stream));
-  HIP_TRY(h, hipMemcpy2D(L, h->K * sizeof(float), base, h->Kp * sizeof(float), h->K * sizeof(float),
-                         static_cast<size_t>(h->N), hipMemcpyDeviceToHost));
-  HIP_TRY(h, hipMemcpy2D(R, h->K * sizeof(float), base + h->N * h->Kp, h->Kp * sizeof(float),
-                         h->K * sizeof(float), static_cast<size_t>(h->M), hipMemcpyDeviceToHost));
-  return PS_MF_OK;
+  if ((r = rows_to_host(h, base, h->N, L))) return r;
+  return rows_to_host(h, base + h->N * h->Kp, h->M, R);
 }
 
 int ps_mf_get_factors(ps_mf_t *h, float *L, float *R) {
