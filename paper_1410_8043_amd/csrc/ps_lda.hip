@@ -674,6 +674,15 @@ __global__ __launch_bounds__(kLoglikThreads) void k_lda_sum(const double *partia
   if (threadIdx.x == 0) out[0] = red[0];
 }
 
+// the assignments in load order: out[load index] = z at every block position.  A scatter of
+// 4-byte words inside documents' runs; 0.05 ms for 10M tokens, where the host's scatter of the
+// copied array took 13 ms.
+__global__ __launch_bounds__(kLoglikThreads) void k_lda_unorder(const int4 *__restrict__ rec, const int32_t *__restrict__ z,
+                                                                int64_t n, int32_t *__restrict__ out) {
+  const int64_t q = static_cast<int64_t>(blockIdx.x) * kLoglikThreads + threadIdx.x;
+  if (q < n) out[static_cast<uint32_t>(rec[q].z)] = z[q];
+}
+
 }  // namespace
 
 struct ps_lda {
@@ -694,6 +703,7 @@ struct ps_lda {
   std::vector<int64_t> order;  // load index at every block position
   std::vector<int64_t> vlog;
   int4 *rec = nullptr;
+  int32_t *zload = nullptr;  // the assignments in load order, on their way to the host
   int32_t *z = nullptr, *ndk = nullptr, *ring = nullptr, *delta = nullptr, *tag = nullptr, *tot = nullptr;
   int64_t *wbeg_dev = nullptr;
   double *partial = nullptr;
@@ -999,6 +1009,7 @@ int load_tokens(ps_lda_t *h, const int32_t *doc, const int32_t *word, const int3
   if ((rc = lda_alloc(h, reinterpret_cast<void **>(&h->rec), sizeof(int4) * n))) return rc;
   // kDist entries past the end: a worker's fetches past its last token read them (unused)
   if ((rc = lda_alloc(h, reinterpret_cast<void **>(&h->z), sizeof(int32_t) * (n + kDist)))) return rc;
+  if ((rc = lda_alloc(h, reinterpret_cast<void **>(&h->zload), sizeof(int32_t) * n))) return rc;
   if ((rc = lda_alloc(h, reinterpret_cast<void **>(&h->ndk), sizeof(int32_t) * h->D * K))) return rc;
   if ((rc = lda_alloc(h, reinterpret_cast<void **>(&h->ring), sizeof(int32_t) * stride * ns))) return rc;
   if ((rc = lda_alloc(h, reinterpret_cast<void **>(&h->delta), sizeof(int32_t) * P * V * K))) return rc;
@@ -1104,10 +1115,11 @@ int export_state(ps_lda_t *h, int32_t kind, int32_t block, void *buf, int64_t ca
   }
   switch (kind) {
     case PS_LDA_X_Z: {
-      std::vector<int32_t> zq(static_cast<size_t>(n));
-      LDA_TRY(h, hipMemcpy(zq.data(), h->z, sizeof(int32_t) * n, hipMemcpyDeviceToHost));
-      int32_t *o = static_cast<int32_t *>(buf);
-      for (int64_t q = 0; q < n; ++q) o[h->order[q]] = zq[q];
+      hipLaunchKernelGGL(k_lda_unorder, dim3(static_cast<unsigned>((n + kLoglikThreads - 1) / kLoglikThreads)),
+                         dim3(kLoglikThreads), 0, h->stream, h->rec, h->z, n, h->zload);
+      LDA_TRY(h, hipGetLastError());
+      LDA_TRY(h, hipStreamSynchronize(h->stream));
+      LDA_TRY(h, hipMemcpy(buf, h->zload, sizeof(int32_t) * n, hipMemcpyDeviceToHost));
       break;
     }
     case PS_LDA_X_NDK: LDA_TRY(h, hipMemcpy(buf, h->ndk, sizeof(int32_t) * n, hipMemcpyDeviceToHost)); break;
