@@ -2,6 +2,7 @@
 #include "layout.h"
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cmath>
 #include <cstring>
@@ -739,6 +740,113 @@ void build_dense(const LayoutParams &p, const BlockLayout &L, const std::vector<
   DU.nnz = DI.nnz = nd;
 }
 
+// The sequential step's lists of one block (see SeqSet): chains_of[w] are worker w's chains.
+void build_seq_lists(const LayoutParams &p, BlockLayout &L, const std::vector<std::vector<int64_t>> &chains_of) {
+  SeqSet &S = L.seq;
+  const int64_t P = p.workers, M = p.items, D = p.seq_list_ahead;
+  if (L.nnz == 0 || p.seq_list_ahead == 0) return;
+  // Lists or chains, by what each was measured to take (us, MI355X):
+  //   chains: a launch per sub-epoch, 4.5 and 0.33 per rating of its longest chain;
+  //   lists: the most of 0.045 per rating of the busiest worker (its CU's 16 wavefronts), 0.4 per
+  //   rating of the busiest user (one after the other) and 2 per rating of a worker's most rated
+  //   item (handed from list to list).
+  // Measured lists / chains, ms per clock of the block: 20K ratings, P = 4: 0.20 / 1.22; 225K, K =
+  // 64, P = 32: 0.50 / 1.41; 2.4M, K = 128, P = 64: 1.57 / 2.60, P = 16: 8.5 / 2.98; 4M, K = 32, P =
+  // 256: 0.74 / 2.88; 2M, K = 256, P = 128: 2.70 / 4.53; 9M, K = 128, P = 64: 7.5 / 6.4; 200K, P = 1:
+  // 18 / 2.6.
+  double t_chains = 0;
+  for (int64_t t = 0; t < S.G; ++t) {
+    int64_t most = 0;
+    for (int64_t ch = S.epoch_chain[t]; ch < S.epoch_chain[t + 1]; ++ch)
+      most = std::max(most, S.chain_beg[ch + 1] - S.chain_beg[ch]);
+    t_chains += most > 0 ? 4.5 + 0.33 * static_cast<double>(most) : 0.0;
+  }
+  int64_t worker_most = 0, item_most = 0;
+  const int64_t user_most = *std::max_element(L.ucount.begin(), L.ucount.end());
+  {
+    std::vector<int64_t> seen(static_cast<size_t>(M), 0);  // ratings of the item in the workers up to w
+    std::vector<int64_t> before(static_cast<size_t>(M), 0), stamp(static_cast<size_t>(M), -1);
+    for (int64_t w = 0; w < P; ++w) {
+      int64_t work = 0;
+      for (int64_t ch : chains_of[w]) {
+        work += S.chain_beg[ch + 1] - S.chain_beg[ch];
+        for (int64_t x = S.chain_beg[ch]; x < S.chain_beg[ch + 1]; ++x) {
+          const int32_t j = S.item[x];
+          if (stamp[j] != w) {
+            stamp[j] = w;
+            before[j] = seen[j];
+          }
+          item_most = std::max(item_most, ++seen[j] - before[j]);
+        }
+      }
+      worker_most = std::max(worker_most, work);
+    }
+  }
+  const double t_lists = std::max({0.045 * static_cast<double>(worker_most), 0.4 * static_cast<double>(user_most),
+                                   2.0 * static_cast<double>(item_most)});
+  if (t_lists >= t_chains || worker_most > kSeqListMost) return;
+  // each worker's users to its lists: the busiest user first, to the shortest list so far
+  std::vector<std::vector<int32_t>> users_of(static_cast<size_t>(P));
+  for (int64_t i = 0; i < p.users; ++i)
+    if (L.ucount[i] > 0) users_of[p.owner[i]].push_back(static_cast<int32_t>(i));
+  std::vector<uint8_t> list_of(static_cast<size_t>(p.users), 0);
+  S.list_beg.assign(static_cast<size_t>(P) * kSeqLists + 1, 0);
+  for (int64_t w = 0; w < P; ++w) {
+    std::vector<int32_t> &us = users_of[w];
+    std::stable_sort(us.begin(), us.end(), [&](int32_t x, int32_t y) { return L.ucount[x] > L.ucount[y]; });
+    int64_t len[kSeqLists] = {};
+    for (int32_t i : us) {
+      int best = 0;
+      for (int l = 1; l < kSeqLists; ++l)
+        if (len[l] < len[best]) best = l;
+      list_of[i] = static_cast<uint8_t>(best);
+      len[best] += L.ucount[i];
+    }
+    for (int l = 0; l < kSeqLists; ++l) S.list_beg[w * kSeqLists + l + 1] = static_cast<int32_t>(len[l]);
+  }
+  for (size_t q = 1; q < S.list_beg.size(); ++q) S.list_beg[q] += S.list_beg[q - 1];
+  S.list_rec.resize(static_cast<size_t>(L.nnz) * 4);
+  struct Last {
+    int32_t worker = -1, list = 0, at = 0;
+  };
+  // worker w is task w mod T's; everything the threads write to is allocated here
+  const int64_t T = L.nnz < (1 << 16) ? 1 : std::min<int64_t>(p.threads, P);
+  std::vector<std::vector<Last>> item_last(static_cast<size_t>(T), std::vector<Last>(static_cast<size_t>(M)));
+  std::vector<int32_t> user_last(static_cast<size_t>(p.users), -1);  // the place of the user's latest rating
+  parallel_for(static_cast<int>(T), T << 16, [&](int64_t lo, int64_t hi) {
+    for (int64_t task = (lo + 0xffff) >> 16; task < (hi + 0xffff) >> 16; ++task)
+      for (int64_t w = task; w < P; w += T) {
+        int32_t done[kSeqLists] = {};
+        for (int64_t ch : chains_of[w])
+          for (int64_t x = S.chain_beg[ch]; x < S.chain_beg[ch + 1]; ++x) {
+            const int32_t i = S.user[x], j = S.item[x];
+            const int l = list_of[i];
+            const int32_t t = done[l]++, prev = user_last[i];
+            int32_t f = S.flag[x] & kSeqFirstR;
+            if (prev < 0) f |= kSeqRunStart | kSeqFirstL;
+            else if (prev != t - 1) f |= kSeqRunStart | (t - D < prev + 1 ? kSeqLateL : 0);
+            user_last[i] = t;
+            Last &b = item_last[task][j];
+            if (b.worker == w) {
+              if (b.list != l)
+                f |= (b.list << kSeqDepListShift) |
+                     static_cast<int32_t>(static_cast<uint32_t>(b.at + 1) << kSeqDepCountShift);
+              else if (t - b.at <= D)
+                f |= (t - b.at) << kSeqDistShift;
+            }
+            b.worker = static_cast<int32_t>(w);
+            b.list = l;
+            b.at = t;
+            int32_t *r = &S.list_rec[4 * (static_cast<size_t>(S.list_beg[w * kSeqLists + l]) + t)];
+            r[0] = i;
+            r[1] = j;
+            std::memcpy(r + 2, &S.val[x], sizeof(float));
+            r[3] = f;
+          }
+      }
+  });
+}
+
 // The sequential step's order of one block (see SeqSet).
 void build_seq(const LayoutParams &p, BlockLayout &L, const std::vector<int32_t> &ent_user) {
   const int64_t nb = L.nnz, M = p.items, G = p.seq_groups, P = p.workers;
@@ -823,6 +931,7 @@ void build_seq(const LayoutParams &p, BlockLayout &L, const std::vector<int32_t>
   S.item_workers.resize(pair_item.size());
   std::vector<int64_t> fill(S.item_wptr.begin(), S.item_wptr.end() - 1);
   for (size_t q = 0; q < pair_item.size(); ++q) S.item_workers[fill[pair_item[q]]++] = pair_worker[q];
+  build_seq_lists(p, L, chains_of);
 }
 
 }  // namespace
@@ -1264,6 +1373,63 @@ int check_dense_twins(const DenseSet &U, const DenseSet &I, std::string &err) {
   return 0;
 }
 
+// the lists by brute force: replayed one rating at a time in application order, every rating is
+// the next of its user's list, its flags say where the latest earlier ratings of its user and
+// of its item lie, and all the lists end together
+int check_seq_lists(const LayoutParams &p, const BlockLayout &L, std::string &err) {
+  const SeqSet &S = L.seq;
+  if (S.list_beg.empty()) return 0;
+  const int64_t P = p.workers, D = p.seq_list_ahead;
+  auto bad = [&](const std::string &what) {
+    err = "sequential lists: " + what;
+    return -1;
+  };
+  if (S.list_beg.size() != static_cast<size_t>(P) * kSeqLists + 1 || S.list_rec.size() != static_cast<size_t>(L.nnz) * 4 ||
+      S.list_beg[0] != 0 || S.list_beg.back() != L.nnz)
+    return bad("array sizes");
+  std::vector<int64_t> list_of(static_cast<size_t>(p.users), -1), user_at(static_cast<size_t>(p.users), -1);
+  for (int64_t q = 0; q < P * kSeqLists; ++q) {
+    if (S.list_beg[q + 1] < S.list_beg[q]) return bad("bounds");
+    for (int64_t r = S.list_beg[q]; r < S.list_beg[q + 1]; ++r) {
+      const int32_t i = S.list_rec[4 * r];
+      if (i < 0 || i >= p.users || p.owner[i] != q / kSeqLists || (list_of[i] >= 0 && list_of[i] != q))
+        return bad("user of entry " + std::to_string(r));
+      list_of[i] = q;
+    }
+  }
+  std::vector<int64_t> done(static_cast<size_t>(P) * kSeqLists, 0);
+  std::vector<std::vector<std::array<int64_t, 3>>> item_at(static_cast<size_t>(p.items));  // (worker, list, place)
+  for (int64_t x = 0; x < L.nnz; ++x) {
+    const int32_t i = S.user[x], j = S.item[x];
+    const int64_t q = list_of[i];
+    if (q < 0) return bad("user " + std::to_string(i) + " has no list");
+    const int64_t t = done[q]++, w = p.owner[i], r = S.list_beg[q] + t;
+    if (r >= S.list_beg[q + 1]) return bad("list " + std::to_string(q) + " is too short");
+    const int32_t *e = &S.list_rec[4 * r];
+    if (e[0] != i || e[1] != j || std::memcmp(e + 2, &S.val[x], sizeof(float)) != 0)
+      return bad("entry " + std::to_string(r) + " differs from its rating");
+    int64_t want = 0;
+    if (user_at[i] != t - 1 || t == 0) want |= kSeqRunStart;
+    if (user_at[i] < 0) want |= kSeqFirstL;
+    else if ((want & kSeqRunStart) && t - D <= user_at[i]) want |= kSeqLateL;
+    user_at[i] = t;
+    bool found = false;
+    for (auto &at : item_at[j])
+      if (at[0] == w) {
+        found = true;
+        if (at[1] != q) want |= ((at[1] % kSeqLists) << kSeqDepListShift) | ((at[2] + 1) << kSeqDepCountShift);
+        else if (t - at[2] <= D) want |= (t - at[2]) << kSeqDistShift;
+        at = {w, q, t};
+      }
+    if (!found) {
+      want |= kSeqFirstR;
+      item_at[j].push_back({w, q, t});
+    }
+    if (static_cast<uint32_t>(e[3]) != static_cast<uint32_t>(want)) return bad("flags of entry " + std::to_string(r));
+  }
+  return 0;
+}
+
 // the sequential step's order against its definition, recomputed entry by entry
 int check_seq(const LayoutParams &p, const BlockLayout &L, std::string &err) {
   const SeqSet &S = L.seq;
@@ -1342,7 +1508,7 @@ int check_seq(const LayoutParams &p, const BlockLayout &L, std::string &err) {
         !std::equal(w.begin(), w.end(), S.item_workers.begin() + S.item_wptr[j]))
       return bad("workers of item " + std::to_string(j));
   }
-  return 0;
+  return check_seq_lists(p, L, err);
 }
 
 }  // namespace

@@ -134,7 +134,25 @@ struct SeqSet {
   std::vector<int32_t> canon;         // [nnz] canonical position of each rating (host only)
   std::vector<int64_t> item_wptr;     // [items + 1]
   std::vector<int32_t> item_workers;  // the workers with a rating of item j, ascending
+  // Lists (where they are estimated faster than the chains): each worker's ratings once more,
+  // dealt to kSeqLists lists by user (all of a user's ratings in one list, the lists about
+  // equally long), each list in application order.  A list is one wavefront's work: it keeps
+  // its users' rows to itself, and waits for another list only where the latest earlier
+  // rating of the same item by the worker lies there.  Any such run applies every row's
+  // updates in the order of the definition, so the results are those of the chains.
+  std::vector<int32_t> list_beg;  // [P * kSeqLists + 1] into list_rec
+  std::vector<int32_t> list_rec;  // [4 * nnz] (user, item, value bits, flags)
 };
+// Flags of a list's rating: kSeqFirstL, kSeqRunStart (a run: consecutive ratings of one user in
+// the list), kSeqFirstR as above; kSeqLateL on a run start whose user's previous run ended too
+// few ratings before for its row, fetched seq_list_ahead ratings ahead, to hold that run's
+// store; bits 4..7 the distance to the latest earlier rating of the same item when that lies
+// at most seq_list_ahead back in the same list; bits 8..11 the list and bits 12..31 the number
+// of ratings that must be done there before the item's row may be read (0: none).
+constexpr int kSeqLists = 16;
+constexpr uint8_t kSeqLateL = 8;
+constexpr int kSeqDepListShift = 8, kSeqDepCountShift = 12;
+constexpr int64_t kSeqListMost = (int64_t{1} << 20) - 1;  // ratings of a worker, so that the count can name each
 
 struct BlockLayout {
   int64_t nnz = 0;
@@ -176,6 +194,7 @@ struct LayoutParams {
   int32_t min_cell_steps = 4;       // runs of cells and dense cells are not cut below this many
                                     // steps (each cut costs every row of the cell a partial row)
   int32_t workers = 1;              // P
+  int32_t seq_list_ahead = 4;       // ratings that a list's rows are fetched ahead, at most 15 (0: no lists)
   int32_t seq_groups = 0;           // G > 0: build the sequential step's order (SeqSet) instead of
                                     // units, cells and dense tiles
 };

@@ -1287,14 +1287,15 @@ __device__ __forceinline__ void wave_store_row(float *__restrict__ row, const fl
   }
 }
 
-// sum over the 64 lanes: the 16-lane row sums, then the four rows through scalar registers
+// sum over the 64 lanes: the 16-lane row sums r0 .. r3, then (r0 + r1) + (r2 + r3) by swapping
+// odd with even rows and the upper with the lower half of two copies (gfx950's permlane swaps):
+// every lane gets the total without a trip through scalar registers, on the chain's critical path
 __device__ __forceinline__ float wave_sum(float v) {
   v = group_sum<16>(v);
-  const float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
-  const float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
-  const float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
-  const float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
-  return (r0 + r1) + (r2 + r3);
+  const auto rows = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(rows[0]) + __uint_as_float(rows[1]);
+  const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
 }
 
 // f(integral_constant<int, K>, base + K) for K = K0 .. N-1 while f returns true
@@ -1385,6 +1386,174 @@ __global__ __launch_bounds__(kBlock) void k_seq(SeqArgs a, int64_t c0, int64_t c
   };
   for (int64_t base = beg; base < end; base += D2) seq_unrolled<0, D2>(step, base);
   if (cur >= 0) wave_store_row<E>(a.lwork + static_cast<int64_t>(cur) * Kp, x, lane, Kp);
+}
+
+// The same step for blocks whose workers have few enough ratings (layout.cpp holds the rule): one
+// workgroup per worker, one wavefront per list of its ratings (layout.h), one launch per clock.
+// A launch per sub-epoch costs about 5 us however few ratings it holds; here a wavefront waits
+// for another one only where a rating's item row was last written by that one, so nothing
+// waits for a whole sub-epoch.  Bound by a wavefront's own instructions: about 110 a rating,
+// 0.33 us when alone on its SIMD, which the busiest user's ratings run through one by one (225K
+// ratings at K = 64, P = 32: 0.50 ms, was 1.41; 2.4M at K = 128, P = 64: 1.57 ms, was 2.60).
+// * done[l] (LDS) counts the ratings of list l that are done.  It is stored with release order
+//   at workgroup scope after the rating's row, and read with acquire order before a row that
+//   depends on it is loaded; the wavefronts of a workgroup share a CU and its first-level cache,
+//   so neither costs a wait for the vector memory.
+// * A rating whose item row was last written in another list is fetched ahead (D ratings) only
+//   if that list's count says so already; otherwise it is fetched when its turn comes, after a
+//   wait for the count.  A rating waits only for ratings before it in the application order, and
+//   a wavefront that waits has published all it has done: the earliest unfinished rating of a
+//   worker never waits, so every wait ends.
+// * Row loads and stores are issued on every path (a row that is not needed is replaced by a row
+//   of zeros), so that the waits before a use count exactly the operations after the load.
+struct SeqListArgs {
+  SeqArgs s;                // rec: the records in list order
+  const int32_t *list_beg;  // [P * kSeqLists + 1]
+  const float *zero;        // Kp zeros
+};
+// ratings a list's rows are fetched ahead, for E floats per lane.  2, 3, 4, 6 and 8 measured
+// within 8% of each other from E = 1 to 4 (2.4M ratings at K = 128: 1.9, 1.68, 1.57, 1.58, 1.63 ms):
+// further ahead, more ratings find their item's row not yet stored by the other list.
+constexpr int seq_list_ahead(int E) { return E >= 8 ? 2 : 4; }
+
+template <int E, bool PerRow>
+__global__ __launch_bounds__(64 * psmf::kSeqLists) void k_seq_lists(SeqListArgs q) {
+  constexpr int D = seq_list_ahead(E);
+  constexpr int kStep = (64 - D) / D * D;  // ratings per block of records, at most 64 - D
+  const SeqArgs &a = q.s;
+  __shared__ int done[psmf::kSeqLists + 64];  // the other lanes' places of a store follow the counts
+  if (threadIdx.x < psmf::kSeqLists) done[threadIdx.x] = 0;
+  __syncthreads();
+  const int lane = static_cast<int>(threadIdx.x) % 64, Kp = a.Kp;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / 64);
+  int *const mine = &done[lane == 0 ? wave : psmf::kSeqLists + lane];
+  const int32_t p = static_cast<int32_t>(blockIdx.x);
+  const int32_t beg = q.list_beg[p * psmf::kSeqLists + wave], n = q.list_beg[p * psmf::kSeqLists + wave + 1] - beg;
+  if (n == 0) return;  // no rating waits for an empty list
+  const int32_t cls = a.wcls[p];
+  const float *Lv = a.ring + a.cls_slot[cls] * a.slot_stride;
+  const float *Rv = Lv + a.r_off;
+  float *Rw = a.rwork + static_cast<int64_t>(p) * a.rwork_stride;
+  const i32x4 *rec = a.rec + beg;
+  // a row's address; a table has fewer than 2^32 bytes
+  const uint32_t row_bytes = static_cast<uint32_t>(Kp) * 4u;
+  auto row_in = [&](const float *table, int32_t r) {
+    return reinterpret_cast<const float *>(reinterpret_cast<const char *>(table) + static_cast<uint32_t>(r) * row_bytes);
+  };
+  auto out_row = [&](float *table, int32_t r) {
+    return reinterpret_cast<float *>(reinterpret_cast<char *>(table) + static_cast<uint32_t>(r) * row_bytes);
+  };
+  auto view_L = [&](int32_t i) { return PerRow ? a.ring + a.rs_u[i] * a.slot_stride : Lv; };
+  auto view_R = [&](int32_t j) {
+    return PerRow ? a.ring + a.rs_i[cls * a.items + j] * a.slot_stride + a.r_off : Rv;
+  };
+  auto count_of = [&](int flags) { return static_cast<int>(static_cast<uint32_t>(flags) >> psmf::kSeqDepCountShift); };
+  auto list_of = [&](int flags) { return (flags >> psmf::kSeqDepListShift) & (psmf::kSeqLists - 1); };
+  auto publish = [&](int count) {
+    __hip_atomic_store(mine, count, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  int base = 0;
+  i32x4 rv = rec[min(lane, n - 1)], rv_next = rec[min(kStep + lane, n - 1)];
+  auto field = [&](int i, int f) { return __builtin_amdgcn_readlane(rv[f], i - base); };
+  int item[D], flag[D];
+  bool late[D];  // the item row was not ready to be fetched ahead
+  float yq[D][E], lq[D][E], wq[D][E];
+  // rows of rating i (ring place K); seen: the other lists' counts, one per lane
+  auto fetch = [&](auto kc, int i, int seen) {
+    constexpr int K = decltype(kc)::value;
+    item[K] = field(i, 1);
+    flag[K] = field(i, 3);
+    late[K] = __builtin_amdgcn_readlane(seen, list_of(flag[K])) < count_of(flag[K]);
+    const float *y = (flag[K] & psmf::kSeqFirstR) ? view_R(item[K]) : Rw;
+    wave_load_row<E>(yq[K], late[K] ? q.zero : row_in(y, item[K]), lane, Kp);
+    const bool own = (flag[K] & (psmf::kSeqRunStart | psmf::kSeqLateL)) == psmf::kSeqRunStart;
+    const int32_t u = field(i, 0);
+    const float *x = (flag[K] & psmf::kSeqFirstL) ? view_L(u) : a.lwork;
+    wave_load_row<E>(lq[K], own ? row_in(x, u) : q.zero, lane, Kp);
+  };
+  // a row loaded and waited for on its own rare path (a load still in flight where the paths
+  // join would make the common path wait for all of its own)
+  auto load_now = [&](float (&d)[E], const float *row) {
+    wave_load_row<E>(d, row, lane, Kp);
+#pragma unroll
+    for (int e = 0; e < E; ++e) asm volatile("" : "+v"(d[e]));
+  };
+  auto counts = [&]() {
+    return __hip_atomic_load(&done[lane % psmf::kSeqLists], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  float x[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) x[e] = 0.f;
+  int32_t cur = -1;
+  auto first = [&](auto kc, int i) {
+    fetch(kc, i, 0);
+    __builtin_amdgcn_sched_barrier(0);  // in this order: the waits count on it
+    return true;
+  };
+  seq_unrolled<0, D>(first, 0);  // past the list's end: the last record again, never used
+  auto step = [&](auto kc, int64_t at) -> bool {
+    constexpr int K = decltype(kc)::value;
+    const int i = static_cast<int>(at);
+    const int flags = flag[K], j = item[K];
+    const float val = __int_as_float(field(i, 2));
+    const int seen = counts();  // waited for where the next row is fetched
+    if (late[K]) {
+      const int l = list_of(flags), need = count_of(flags);
+      while (__builtin_amdgcn_readlane(counts(), l) < need) __builtin_amdgcn_s_sleep(1);
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      load_now(yq[K], row_in(Rw, j));
+    }
+    if (flags & psmf::kSeqRunStart) {
+      if (cur >= 0) wave_store_row<E>(out_row(a.lwork, cur), x, lane, Kp);
+      cur = field(i, 0);
+      if (flags & psmf::kSeqLateL) load_now(lq[K], row_in(a.lwork, cur));
+#pragma unroll
+      for (int e = 0; e < E; ++e) x[e] = lq[K][e];
+    }
+    float y[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) y[e] = yq[K][e];
+    const int dist = (flags >> psmf::kSeqDistShift) & 15;
+    if (dist) {  // the row rating i - dist wrote
+#pragma unroll
+      for (int d = 1; d <= D; ++d)
+        if (dist == d) {
+#pragma unroll
+          for (int e = 0; e < E; ++e) y[e] = wq[(K - d + 2 * D) % D][e];
+        }
+    }
+    float dot = 0.f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) dot = fmaf(x[e], y[e], dot);
+    const float err = val - wave_sum(dot);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const float xl = x[e], yl = y[e];
+      x[e] = fmaf(a.eta, fmaf(err, yl, -a.lambda * xl), xl);
+      y[e] = fmaf(a.eta, fmaf(err, xl, -a.lambda * yl), yl);
+    }
+    wave_store_row<E>(out_row(Rw, j), y, lane, Kp);
+#pragma unroll
+    for (int e = 0; e < E; ++e) wq[K][e] = y[e];
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");  // the counts, before the rows they vouch for
+    fetch(kc, i + D, seen);
+    publish(i + 1);  // after the fetch: the fence would wait for this store
+    return true;
+  };
+  auto last = [&](auto kc, int64_t at) -> bool { return at < n && step(kc, at); };
+  // whole rotations without an exit inside (an exit would join the loop's back edge with its
+  // latest loads still in flight), then the last ratings
+  int i = 0;
+  for (;;) {
+    const int lim = min(base + kStep, n);
+    for (; i + D <= lim; i += D) seq_unrolled<0, D>(step, i);
+    if (n <= base + kStep) break;
+    base = i;
+    rv = rv_next;
+    rv_next = rec[min(base + kStep + lane, n - 1)];
+  }
+  seq_unrolled<0, D>(last, i);
+  wave_store_row<E>(out_row(a.lwork, cur), x, lane, Kp);
 }
 
 struct SeqCommitArgs {
@@ -1562,6 +1731,21 @@ hipError_t dispatch_seq(int Kp, const SeqArgs &a, int64_t c0, int64_t c1, hipStr
   }
 }
 
+template <int E>
+hipError_t launch_seq_lists(const SeqListArgs &a, int32_t P, hipStream_t st) {
+  if (a.s.rs_u) hipLaunchKernelGGL((k_seq_lists<E, true>), dim3(P), dim3(64 * psmf::kSeqLists), 0, st, a);
+  else hipLaunchKernelGGL((k_seq_lists<E, false>), dim3(P), dim3(64 * psmf::kSeqLists), 0, st, a);
+  return hipGetLastError();
+}
+hipError_t dispatch_seq_lists(int Kp, const SeqListArgs &a, int32_t P, hipStream_t st) {
+  switch (Kp) {
+    case 128: return launch_seq_lists<2>(a, P, st);
+    case 256: return launch_seq_lists<4>(a, P, st);
+    case 512: return launch_seq_lists<8>(a, P, st);
+    default: return launch_seq_lists<1>(a, P, st);  // 8 .. 64
+  }
+}
+
 template <bool FromE>
 hipError_t launch_dense(int Kp, const DenseArgs &a, int64_t grid, hipStream_t st) {
   const dim3 gd(static_cast<unsigned>(grid)), bd(kDenseThreads);
@@ -1621,6 +1805,7 @@ struct DeviceSeq {
   int64_t *chain_beg = nullptr, *item_wptr = nullptr;
   int32_t *chain_worker = nullptr, *item_workers = nullptr;
   int32_t *rec = nullptr;            // [nnz * 4] (user, item, value bits, flags)
+  int32_t *list_beg = nullptr;       // the block's ratings are in lists (rec: in list order); null: chains
 };
 
 struct DeviceBlock {
@@ -2091,6 +2276,13 @@ int seq_clock(ps_mf_t *h) {
   hipEvent_t ev = nullptr;
   if ((rc = record(h, &ev))) return rc;
   auto launch_epochs = [&]() -> hipError_t {
+    if (q.list_beg) {
+      SeqListArgs la{};
+      la.s = a;
+      la.list_beg = q.list_beg;
+      la.zero = h->zero_row;
+      return dispatch_seq_lists(h->Kp, la, h->P, h->stream);
+    }
     for (int32_t t = 0; t < h->seq_groups; ++t) {
       const int64_t c0 = q.epoch_chain[t], c1 = q.epoch_chain[t + 1];
       if (c1 > c0) {
@@ -2105,7 +2297,8 @@ int seq_clock(ps_mf_t *h) {
   // HIP graph and replayed: one submission instead of up to G.
   const int64_t rows = 2 * static_cast<int64_t>(h->s) + 1;
   const int64_t key = h->policy == PS_MF_VAP ? b : b * rows + table_row(h, c);
-  if (h->seq_graphs && !h->eta_decay) {
+  const bool graphs = h->seq_graphs && !h->eta_decay && !q.list_beg;
+  if (graphs) {
     if (h->seq_exec.empty()) h->seq_exec.assign(static_cast<size_t>(h->B * rows), nullptr);
     hipGraphExec_t &ex = h->seq_exec[static_cast<size_t>(key)];
     if (!ex) {
@@ -2129,7 +2322,7 @@ int seq_clock(ps_mf_t *h) {
       }
     }
   }
-  if (h->seq_graphs && !h->eta_decay) {
+  if (graphs && h->seq_graphs) {
     HIP_TRY(h, hipGraphLaunch(h->seq_exec[static_cast<size_t>(key)], h->stream));
   } else {
     HIP_TRY(h, launch_epochs());
@@ -2570,6 +2763,7 @@ int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const flo
   lp.workers = h->P;
   if (seq) {
     lp.seq_groups = h->seq_groups;
+    lp.seq_list_ahead = seq_list_ahead(h->Kp / 64);
     lp.dense_min = 0;
     lp.cell_rows = lp.cell_groups = 0;
   }
@@ -2624,15 +2818,19 @@ int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const flo
       const psmf::SeqSet &S = L.seq;
       DeviceSeq &q = d.seq;
       q.epoch_chain = S.epoch_chain;
-      std::vector<int32_t> rec(S.user.size() * 4);
-      for (size_t x = 0; x < S.user.size(); ++x) {
-        rec[4 * x] = S.user[x];
-        rec[4 * x + 1] = S.item[x];
-        std::memcpy(&rec[4 * x + 2], &S.val[x], sizeof(float));
-        rec[4 * x + 3] = S.flag[x];
+      std::vector<int32_t> rec;
+      if (S.list_beg.empty()) {
+        rec.resize(S.user.size() * 4);
+        for (size_t x = 0; x < S.user.size(); ++x) {
+          rec[4 * x] = S.user[x];
+          rec[4 * x + 1] = S.item[x];
+          std::memcpy(&rec[4 * x + 2], &S.val[x], sizeof(float));
+          rec[4 * x + 3] = S.flag[x];
+        }
       }
+      if (!S.list_beg.empty() && (r = upload(h, &q.list_beg, S.list_beg))) return undo(r);
       if ((r = upload(h, &q.chain_beg, S.chain_beg)) || (r = upload(h, &q.chain_worker, S.chain_worker)) ||
-          (r = upload(h, &q.rec, rec)) || (r = upload(h, &q.item_wptr, S.item_wptr)) ||
+          (r = upload(h, &q.rec, S.list_beg.empty() ? rec : S.list_rec)) || (r = upload(h, &q.item_wptr, S.item_wptr)) ||
           (r = upload(h, &q.item_workers, S.item_workers)))
         return undo(r);
     } else if ((r = upload_units(h, d.by_user, L.by_user)) || (r = upload_units(h, d.by_item, L.by_item)) ||
