@@ -42,12 +42,10 @@
 #include "layout.h"
 
 // The fp64 partial sums of the loss for callers that cannot allocate (ps_mf_loss_noalloc):
-// a fixed array in every GPU's memory, held until the process ends.  Entries
-// [0, kNoAllocPartials) take the per-workgroup partials, the last one the final sum.  Host
-// code never passes the array's name to a kernel (on the host it is a stand-in, not a
+// a fixed array in every GPU's memory, held until the process ends.  Host code never passes the array's name to a kernel (on the host it is a stand-in, not a
 // device address): each device's address comes from hipGetSymbolAddress.
 constexpr int64_t kNoAllocPartials = int64_t{1} << 18;  // 2 MiB of partials
-static __device__ __align__(256) double scratch[kNoAllocPartials + 1];
+static __device__ __align__(256) double scratch[kNoAllocPartials];
 
 namespace {
 
@@ -63,7 +61,8 @@ constexpr int kTileFloats = PS_MF_CELL_TILE_FLOATS; // LDS sub-tile of a cell (4
 static_assert(kSweepBlock % 256 == 0 && kSweepBlock <= 1024, "cell workgroups hold whole 256-thread quarters");
 static_assert(kTileFloats % 512 == 0 && kTileFloats * 4 <= 160 * 1024, "a cell sub-tile holds whole 512-wide rows in LDS");
 constexpr int64_t kPackBytes = 16 << 20;  // packed rows moved per copy where rows are padded (K < Kp)
-constexpr int kLossSegment = 512;  // ratings per lane group of the loss
+constexpr int kLossSegment = 64;   // ratings per lane group of the loss
+constexpr int kLossCount = 512;    // ratings per lane group by which the loss's partial sums are counted
 // automatic threshold of the dense (MFMA) tiles: ratings per 64 x 64 tile
 #ifndef PS_MF_DENSE_AUTO
 #define PS_MF_DENSE_AUTO 800
@@ -866,29 +865,60 @@ __global__ __launch_bounds__(kDenseThreads, dense_waves_per_simd<Kp>()) void k_d
 }
 
 // Squared loss over the canonical CSR of a block at one ring slot: one lane group per
-// segment (a user's ratings, cut at kLossSegment), e in fp32, e^2 accumulated in fp64,
-// one partial per workgroup (fixed order, so the result is deterministic).
+// segment (a user's ratings, cut at kLossSegment; further segments at the grid's stride), e in
+// fp32, e^2 accumulated in fp64, one partial per workgroup (fixed order, so the result is
+// deterministic).  Bound by the gathers of the item rows.  The (row, value) pairs are read 8 at a
+// time (from any 4-byte address; both arrays have 8 entries of padding) and the next 8 while
+// the current ones are swept, and several rows are in flight.  One rating at a time, its row
+// waiting for its number, a segment of 512 ratings took 0.2 ms however few there were: 4.9M
+// ratings at K = 64 in 4 blocks 0.90 -> 0.16 ms, 17M at K = 128 0.86 -> 0.41 ms.
+typedef i32x4 __attribute__((aligned(4))) i32x4_any;
+typedef f32x4 __attribute__((aligned(4))) f32x4_any;
 template <int G, int E>
 __global__ __launch_bounds__(kBlock) void k_loss(const int32_t *__restrict__ seg_user,
                                                  const int64_t *__restrict__ seg_beg, int64_t nseg,
                                                  const int32_t *__restrict__ col, const float *__restrict__ val,
                                                  const float *__restrict__ L, const float *__restrict__ R,
-                                                 double *__restrict__ out) {
+                                                 int64_t r_bytes, double *__restrict__ out) {
   constexpr int Kp = G * E;
   constexpr int NG = kBlock / G;
+  constexpr int RF = rows_in_flight<E>();
   __shared__ double acc_sh[NG];
   const int g = threadIdx.x & (G - 1);
   const int grp = threadIdx.x / G;
-  const int64_t sg = static_cast<int64_t>(blockIdx.x) * NG + grp;
+  const __amdgpu_buffer_rsrc_t rows = table_rsrc(R, r_bytes);
   double acc = 0.0;
-  if (sg < nseg) {
+  for (int64_t sg = static_cast<int64_t>(blockIdx.x) * NG + grp; sg < nseg; sg += static_cast<int64_t>(gridDim.x) * NG) {
+    const int64_t beg = seg_beg[sg];
+    const int n = static_cast<int>(seg_beg[sg + 1] - beg);  // 1 .. kLossSegment
+    const int32_t *ci = col + beg;
+    const float *vi = val + beg;
     float x[E];
     load_row<G, E>(x, L + static_cast<int64_t>(seg_user[sg]) * Kp, g);
-    for (int64_t t = seg_beg[sg]; t < seg_beg[sg + 1]; ++t) {
-      float y[E];
-      load_row<G, E>(y, R + static_cast<int64_t>(col[t]) * Kp, g);
-      const float e = residual<G, E>(x, y, val[t]);
-      acc += static_cast<double>(e) * static_cast<double>(e);
+    i32x4 ni0 = *reinterpret_cast<const i32x4_any *>(ci), ni1 = *reinterpret_cast<const i32x4_any *>(ci + 4);
+    f32x4 nv0 = *reinterpret_cast<const f32x4_any *>(vi), nv1 = *reinterpret_cast<const f32x4_any *>(vi + 4);
+    for (int t0 = 0; t0 < n; t0 += 8) {
+      const i32x4 i0 = ni0, i1 = ni1;
+      const f32x4 v0 = nv0, v1 = nv1;
+      if (t0 + 8 < n) {
+        ni0 = *reinterpret_cast<const i32x4_any *>(ci + t0 + 8); ni1 = *reinterpret_cast<const i32x4_any *>(ci + t0 + 12);
+        nv0 = *reinterpret_cast<const f32x4_any *>(vi + t0 + 8); nv1 = *reinterpret_cast<const f32x4_any *>(vi + t0 + 12);
+      }
+      const int idx[8] = {i0[0], i0[1], i0[2], i0[3], i1[0], i1[1], i1[2], i1[3]};
+      const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+#pragma unroll
+      for (int q = 0; q < 8; q += RF) {
+        if (t0 + q >= n) break;
+        float y[RF][E];
+#pragma unroll
+        for (int w = 0; w < RF; ++w)  // entries past the segment read row 0
+          load_row_rsrc<G, E>(y[w], rows, t0 + q + w < n ? static_cast<uint32_t>(idx[q + w]) * (Kp * 4u) : 0u, g);
+#pragma unroll
+        for (int w = 0; w < RF; ++w) {
+          const double e = residual<G, E>(x, y[w], v[q + w]);
+          if (t0 + q + w < n) acc += e * e;
+        }
+      }
     }
   }
   if (g == 0) acc_sh[grp] = acc;
@@ -900,19 +930,22 @@ __global__ __launch_bounds__(kBlock) void k_loss(const int32_t *__restrict__ seg
   }
 }
 
-// fixed-order final sum of the loss partials (deterministic for a given layout)
-__global__ __launch_bounds__(kBlock) void k_sum_partials(const double *__restrict__ partial, int64_t n,
-                                                          double *__restrict__ out) {
-  __shared__ double sh[kBlock];
+// fixed-order final sum of the loss partials (deterministic for a given layout), into host
+// memory; one workgroup, eight partials in flight per thread
+constexpr int kSumThreads = 1024;
+__global__ __launch_bounds__(kSumThreads) void k_sum_partials(const double *__restrict__ partial, int64_t n,
+                                                              double *__restrict__ out) {
+  __shared__ double sh[kSumThreads];
   double s = 0.0;
-  for (int64_t x = threadIdx.x; x < n; x += kBlock) s += partial[x];
+#pragma unroll 8
+  for (int64_t x = threadIdx.x; x < n; x += kSumThreads) s += partial[x];
   sh[threadIdx.x] = s;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double t = 0.0;
-    for (int x = 0; x < kBlock; ++x) t += sh[x];
-    *out = t;
+  for (int o = kSumThreads / 2; o > 0; o >>= 1) {
+    if (static_cast<int>(threadIdx.x) < o) sh[threadIdx.x] += sh[threadIdx.x + o];
+    __syncthreads();
   }
+  if (threadIdx.x == 0) *out = sh[0];
 }
 
 struct FinalArgs {
@@ -1763,9 +1796,10 @@ hipError_t launch_dense(int Kp, const DenseArgs &a, int64_t grid, hipStream_t st
 template <int G, int E>
 struct LaunchLoss {
   static hipError_t run(const int32_t *seg_user, const int64_t *seg_beg, int64_t nseg, const int32_t *col,
-                        const float *val, const float *L, const float *R, int64_t grid, double *out, hipStream_t st) {
+                        const float *val, const float *L, const float *R, int64_t r_bytes, int64_t grid, double *out,
+                        hipStream_t st) {
     hipLaunchKernelGGL((k_loss<G, E>), dim3(static_cast<unsigned>(grid)), dim3(kBlock), 0, st, seg_user, seg_beg,
-                       nseg, col, val, L, R, out);
+                       nseg, col, val, L, R, r_bytes, out);
     return hipGetLastError();
   }
 };
@@ -1888,7 +1922,7 @@ struct ps_mf {
   double *loss_partial = nullptr;
   int64_t loss_partial_len = 0;
   int64_t loss_parts = 0;  // partial sums one loss takes (all blocks)
-  double *loss_out = nullptr;
+  double *loss_out = nullptr;  // pinned host memory that the last loss kernel writes
   std::vector<DeviceBlock> dblocks;
   std::vector<void *> allocations;
   // timing
@@ -1941,6 +1975,15 @@ int dev_alloc(ps_mf_t *h, void **p, size_t bytes) {
 template <class T>
 int upload(ps_mf_t *h, T **dst, const std::vector<T> &src) {
   int rc = dev_alloc(h, reinterpret_cast<void **>(dst), src.size() * sizeof(T));
+  if (rc) return rc;
+  if (!src.empty()) HIP_TRY(h, hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice));
+  return PS_MF_OK;
+}
+
+// with `pad` entries of allocated, unspecified padding after the last
+template <class T>
+int upload_padded(ps_mf_t *h, T **dst, const std::vector<T> &src, size_t pad) {
+  int rc = dev_alloc(h, reinterpret_cast<void **>(dst), (src.size() + pad) * sizeof(T));
   if (rc) return rc;
   if (!src.empty()) HIP_TRY(h, hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice));
   return PS_MF_OK;
@@ -2781,15 +2824,26 @@ int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const flo
   for (int b = 0; b < h->B; ++b)
     for (int64_t i = 0; i < h->N; ++i)
       h->worker_ratings[static_cast<size_t>(b) * h->P + h->owner[i]] += h->layout[b].ucount[i];
-  // partial sums of the loss: one per workgroup of lane groups, a lane group per loss
-  // segment (a user's ratings of a block, cut every kLossSegment)
+  // partial sums of the loss: counted as one per workgroup of lane groups, a lane group per
+  // kLossCount of a user's ratings of a block.  The launches take a workgroup per lane groups of
+  // kLossSegment ratings (more, shorter ones) where those fit the static scratch too, else the
+  // counted ones, each of which then sweeps several segments.
   h->loss_parts = 0;
+  const int64_t groups = kBlock / shape_for(h->Kp).G;
+  std::vector<int64_t> loss_grid(static_cast<size_t>(h->B)), loss_most(static_cast<size_t>(h->B));
+  int64_t loss_most_all = 0;
   for (int b = 0; b < h->B; ++b) {
-    int64_t nseg = 0;
-    for (int64_t i = 0; i < h->N; ++i) nseg += (h->layout[b].ucount[i] + kLossSegment - 1) / kLossSegment;
-    const int64_t groups = kBlock / shape_for(h->Kp).G;
-    h->loss_parts += (nseg + groups - 1) / groups;
+    int64_t counted = 0, nseg = 0;
+    for (int64_t i = 0; i < h->N; ++i) {
+      counted += (h->layout[b].ucount[i] + kLossCount - 1) / kLossCount;
+      nseg += (h->layout[b].ucount[i] + kLossSegment - 1) / kLossSegment;
+    }
+    loss_grid[b] = (counted + groups - 1) / groups;
+    loss_most[b] = (nseg + groups - 1) / groups;
+    h->loss_parts += loss_grid[b];
+    loss_most_all += loss_most[b];
   }
+  if (loss_most_all <= kNoAllocPartials) loss_grid = loss_most;
   if (h->host_only) {
     for (int b = 0; b < h->B; ++b)
       if (psmf::check_layout(lp, h->layout[b], err))
@@ -2811,8 +2865,8 @@ int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const flo
     DeviceBlock &d = h->dblocks[b];
     d.nnz = L.nnz;
     if ((r = upload(h, &d.ucount, L.ucount)) || (r = upload(h, &d.icount, L.icount)) ||
-        (r = upload(h, &d.icount_cls, L.icount_cls)) || (r = upload(h, &d.col, L.col)) ||
-        (r = upload(h, &d.val, L.val)))
+        (r = upload(h, &d.icount_cls, L.icount_cls)) || (r = upload_padded(h, &d.col, L.col, 8)) ||
+        (r = upload_padded(h, &d.val, L.val, 8)))
       return undo(r);
     if (seq) {
       const psmf::SeqSet &S = L.seq;
@@ -2855,7 +2909,7 @@ int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const flo
       d.nseg = static_cast<int64_t>(su.size());
       if ((r = upload(h, &d.seg_user, su)) || (r = upload(h, &d.seg_beg, sb))) return undo(r);
     }
-    d.loss_grid = (d.nseg + kBlock / shape_for(h->Kp).G - 1) / (kBlock / shape_for(h->Kp).G);
+    d.loss_grid = loss_grid[b];
     loss_len += d.loss_grid;
   }
   if ((r = dev_alloc(h, reinterpret_cast<void **>(&h->partial_u), static_cast<size_t>(max_units_u * h->Kp) * sizeof(float))) ||
@@ -2865,12 +2919,17 @@ int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const flo
   std::vector<int32_t> ucls(static_cast<size_t>(h->N));
   for (int64_t i = 0; i < h->N; ++i) ucls[i] = h->cls_of_worker[h->owner[i]];
   if ((r = upload(h, &h->ucls, ucls))) return undo(r);
-  if (loss_len != h->loss_parts) return undo(fail(h, PS_MF_EINTERNAL, "loss partials %lld, expected %lld",
-                                                  (long long)loss_len, (long long)h->loss_parts));
   h->loss_partial_len = std::max<int64_t>(1, loss_len);
   if ((r = dev_alloc(h, reinterpret_cast<void **>(&h->loss_partial), static_cast<size_t>(h->loss_partial_len) * sizeof(double))))
     return undo(r);
-  if ((r = dev_alloc(h, reinterpret_cast<void **>(&h->loss_out), sizeof(double)))) return undo(r);
+  if (!h->loss_out) {
+    const hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&h->loss_out), sizeof(double), hipHostMallocDefault);
+    if (e != hipSuccess) {
+      h->loss_out = nullptr;
+      (void)hipGetLastError();
+      return undo(fail(h, PS_MF_ENOMEM, "hipHostMalloc of the loss: %s", hipGetErrorString(e)));
+    }
+  }
   if ((r = upload(h, &h->zero_row, std::vector<float>(static_cast<size_t>(h->Kp), 0.f)))) return undo(r);
   if (h->K != h->Kp) {
     h->pack_rows = std::min(std::max(h->N, h->M), std::max<int64_t>(1, kPackBytes / (h->K * 4)));
@@ -2947,9 +3006,9 @@ int rows_from_host(ps_mf_t *h, const float *host, int64_t n, float *rows) {
 }
 
 // Squared loss of the latest version: one k_loss launch per block writes its workgroups'
-// fp64 partials into partial[], k_sum_partials adds them in a fixed order into *result
-// (device memory), and the host waits for the value.  Allocates nothing.
-int loss_into(ps_mf_t *h, double *partial, double *result, double *out) {
+// fp64 partials into partial[], k_sum_partials adds them in a fixed order into the handle's
+// pinned host memory, and the host waits for it.  Allocates nothing.
+int loss_into(ps_mf_t *h, double *partial, double *out) {
   const int64_t slot_stride = (h->N + h->M) * h->Kp;
   const int32_t sl = static_cast<int32_t>(h->clock % (h->s + 1));
   const float *L = h->ring + sl * slot_stride;
@@ -2958,20 +3017,18 @@ int loss_into(ps_mf_t *h, double *partial, double *result, double *out) {
   for (int b = 0; b < h->B; ++b) {
     const DeviceBlock &d = h->dblocks[b];
     if (d.nnz == 0) continue;
-    HIP_TRY(h, dispatch<LaunchLoss>(h->Kp, d.seg_user, d.seg_beg, d.nseg, d.col, d.val, L, R, d.loss_grid,
-                                     partial + off, h->stream));
+    HIP_TRY(h, dispatch<LaunchLoss>(h->Kp, d.seg_user, d.seg_beg, d.nseg, d.col, d.val, L, R,
+                                     h->M * h->Kp * 4, d.loss_grid, partial + off, h->stream));
     off += d.loss_grid;
   }
   if (off == 0) {
     *out = 0.0;
     return PS_MF_OK;
   }
-  hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kBlock), 0, h->stream, partial, off, result);
+  hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kSumThreads), 0, h->stream, partial, off, h->loss_out);
   HIP_TRY(h, hipGetLastError());
-  double v = 0;
-  HIP_TRY(h, hipMemcpyAsync(&v, result, sizeof(double), hipMemcpyDeviceToHost, h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));
-  *out = v;
+  *out = *static_cast<volatile double *>(h->loss_out);
   return PS_MF_OK;
 }
 
@@ -3047,7 +3104,7 @@ int ps_mf_loss(ps_mf_t *h, double *out) {
   if (!h->loaded || !h->has_factors) return fail(h, PS_MF_ESTATE, "load ratings and set factors before the loss");
   int r = ensure_device(h);
   if (r) return r;
-  return loss_into(h, h->loss_partial, h->loss_out, out);
+  return loss_into(h, h->loss_partial, out);
 }
 
 int ps_mf_loss_noalloc(ps_mf_t *h, double *out) {
@@ -3061,7 +3118,7 @@ int ps_mf_loss_noalloc(ps_mf_t *h, double *out) {
   if (r) return r;
   double *sc = nullptr;
   if ((r = scratch_address(h, &sc))) return r;
-  return loss_into(h, sc, sc + kNoAllocPartials, out);
+  return loss_into(h, sc, out);
 }
 
 int ps_mf_get_version(ps_mf_t *h, int64_t v, float *L, float *R) {
@@ -3242,6 +3299,7 @@ void ps_mf_destroy(ps_mf_t *h) {
   for (hipGraphExec_t ex : h->sweep_exec)
     if (ex) (void)hipGraphExecDestroy(ex);
   for (void *p : h->allocations) (void)hipFree(p);
+  if (h->loss_out) (void)hipHostFree(h->loss_out);
   if (h->side_stream) (void)hipStreamDestroy(h->side_stream);
   if (h->cell_stream) (void)hipStreamDestroy(h->cell_stream);
   if (h->fork) (void)hipEventDestroy(h->fork);
