@@ -1181,10 +1181,13 @@ __global__ __launch_bounds__(kBlock) void k_poison(FinalArgs fa, CommitArgs ca) 
 // k_vap_norms reduces, for d = 1 .. dmax, the max of the fp32 differences between the
 // slots of versions c and c - d (padding columns are zero in every slot) into this
 // clock's entry of the norm log (float bits, atomicMax over non-negative floats; NaN is
-// ignored): one pass reads every slot once, with the dmax running maxima in registers
-// (dmax <= kVapFused; beyond, one pass per d).  k_vap_pick then writes the slot the sweeps
-// read and the version log entry.
-constexpr int kVapFused = 16;
+// ignored); the last workgroup then writes the slot the sweeps read and the version log entry
+// (k_vap_pick alone does at clocks with no older version).  Each element is read once for every
+// DM versions, whose loads are in flight together.  Bound by HBM and the 256 MB cache before it:
+// at 49,796 rows of 128, s = 3, norms and pick of 102 MB take 20 us (84 us with 2048 workgroups,
+// whose atomics meet on one line, a load at a time in flight and a launch of its own for the pick;
+// 2048, 1024, 512 and 256 workgroups of this form: a clock of 139, 120, 114 and 113 us).
+constexpr int kVapBlocks = 512;
 struct VapArgs {
   const float *ring;
   int64_t slot_stride;
@@ -1192,69 +1195,80 @@ struct VapArgs {
   int64_t c;
   int32_t S1, dmax;
   unsigned *norms;     // [S1] this clock's norms
+  double bound;
+  int32_t *slot;       // the view's slot
+  int64_t *vlog;
+  unsigned *arrived;   // workgroups that are done: 0 before and after every launch
 };
 
 __device__ __forceinline__ float f4_absdiff_max(const float4 x, const float4 y) {
   return fmaxf(fmaxf(fabsf(x.x - y.x), fabsf(x.y - y.y)), fmaxf(fabsf(x.z - y.z), fabsf(x.w - y.w)));
 }
 
-// block max of m (every thread passes its value), added to *out by atomicMax
-__device__ __forceinline__ void vap_block_max(float m, float *red, unsigned *out) {
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x / 64] = m;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float t = red[0];
-    for (int w = 1; w < kBlock / 64; ++w) t = fmaxf(t, red[w]);
-    atomicMax(out, __float_as_uint(t));
+__device__ __forceinline__ void vap_pick(const VapArgs &a) {
+  int32_t d = 0;
+  for (int32_t k = 1; k <= a.dmax; ++k) {
+    const unsigned bits = __hip_atomic_load(a.norms + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (static_cast<double>(__uint_as_float(bits)) <= a.bound) d = k;
   }
-  __syncthreads();
+  a.slot[0] = static_cast<int32_t>((a.c - d) % a.S1);
+  a.vlog[a.c] = a.c - d;
 }
 
+template <int DM>
 __global__ __launch_bounds__(kBlock) void k_vap_norms(VapArgs a) {
-  __shared__ float red[kBlock / 64];
+  __shared__ float red[kBlock / 64][DM];
   const float4 *r4 = reinterpret_cast<const float4 *>(a.ring);
   const int64_t ss4 = a.slot_stride / 4;
-  const int32_t slot_c = static_cast<int32_t>(a.c % a.S1);
-  if (a.dmax <= kVapFused) {
-    float m[kVapFused];
-    int32_t sd[kVapFused];
+  const float4 *now = r4 + (a.c % a.S1) * ss4;
+  for (int32_t d0 = 1; d0 <= a.dmax; d0 += DM) {
+    const float4 *then[DM];
+    float m[DM];
 #pragma unroll
-    for (int d = 0; d < kVapFused; ++d) {
+    for (int d = 0; d < DM; ++d) {
       m[d] = 0.f;
-      sd[d] = static_cast<int32_t>((a.c - d - 1 + (a.c < d + 1 ? a.S1 : 0)) % a.S1);  // used for d < dmax only
+      then[d] = r4 + (d0 + d <= a.dmax ? (a.c - d0 - d) % a.S1 : a.c % a.S1) * ss4;  // past dmax: no difference
     }
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < a.n4;
          i += static_cast<int64_t>(gridDim.x) * kBlock) {
-      const float4 x = r4[slot_c * ss4 + i];
+      const float4 x = now[i];
+      float4 y[DM];
 #pragma unroll
-      for (int d = 0; d < kVapFused; ++d)
-        if (d < a.dmax) m[d] = fmaxf(m[d], f4_absdiff_max(x, r4[sd[d] * ss4 + i]));
+      for (int d = 0; d < DM; ++d) y[d] = then[d][i];
+#pragma unroll
+      for (int d = 0; d < DM; ++d) m[d] = fmaxf(m[d], f4_absdiff_max(x, y[d]));
     }
 #pragma unroll
-    for (int d = 0; d < kVapFused; ++d)
-      if (d < a.dmax) vap_block_max(m[d], red, a.norms + d + 1);
-    return;
+    for (int d = 0; d < DM; ++d) {
+      for (int o = 32; o > 0; o >>= 1) m[d] = fmaxf(m[d], __shfl_xor(m[d], o));
+      if ((threadIdx.x & 63) == 0) red[threadIdx.x / 64][d] = m[d];
+    }
+    __syncthreads();
+    const int d = static_cast<int>(threadIdx.x);
+    if (d < DM && d0 + d <= a.dmax) {
+      float t = red[0][d];
+      for (int w = 1; w < kBlock / 64; ++w) t = fmaxf(t, red[w][d]);
+      // most workgroups find a larger norm there already
+      unsigned *at = a.norms + d0 + d;
+      if (__hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < __float_as_uint(t))
+        atomicMax(at, __float_as_uint(t));
+    }
+    __syncthreads();
   }
-  for (int d = 1; d <= a.dmax; ++d) {
-    const int32_t sd = static_cast<int32_t>((a.c - d) % a.S1);
-    float m = 0.f;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < a.n4;
-         i += static_cast<int64_t>(gridDim.x) * kBlock) {
-      m = fmaxf(m, f4_absdiff_max(r4[slot_c * ss4 + i], r4[sd * ss4 + i]));
+  // The workgroups tell each other nothing but the norms, by device-wide atomics of this first
+  // wavefront: once those are complete it may count the workgroup in.  (A release fence would
+  // write back the whole L2, once per workgroup: 25 us a launch.)
+  if (threadIdx.x < 64) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (threadIdx.x == 0 && atomicAdd(a.arrived, 1u) == gridDim.x - 1) {
+      vap_pick(a);
+      __hip_atomic_store(a.arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    vap_block_max(m, red, a.norms + d);
   }
 }
 
-__global__ void k_vap_pick(const unsigned *norms, int32_t dmax, double bound, int64_t c, int32_t S1, int32_t *slot,
-                           int64_t *vlog) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  int32_t d = 0;
-  for (int32_t k = 1; k <= dmax; ++k)
-    if (static_cast<double>(__uint_as_float(norms[k])) <= bound) d = k;
-  slot[0] = static_cast<int32_t>((c - d) % S1);
-  vlog[c] = c - d;
+__global__ void k_vap_pick(VapArgs a) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) vap_pick(a);
 }
 
 // ------------------------------------------------------------------ sequential step
@@ -1917,7 +1931,7 @@ struct ps_mf {
   // VAP: the slot of the current clock's view, the version read and the norms of every clock
   int32_t *vap_slot = nullptr;
   int64_t *vap_v = nullptr;
-  unsigned *vap_norms = nullptr;
+  unsigned *vap_norms = nullptr, *vap_arrived = nullptr;
   int64_t vap_cap = 0;
   double *loss_partial = nullptr;
   int64_t loss_partial_len = 0;
@@ -2253,21 +2267,24 @@ int clock_views(ps_mf_t *h, int64_t c, const int32_t **cls_slot) {
   if (r) return r;
   const int32_t S1 = h->s + 1, dmax = static_cast<int32_t>(std::min<int64_t>(c, h->s));
   unsigned *norms = h->vap_norms + c * S1;
-  if (dmax > 0) {
-    VapArgs a{};
-    a.ring = h->ring;
-    a.slot_stride = (h->N + h->M) * h->Kp;
-    a.n4 = a.slot_stride / 4;
-    a.c = c;
-    a.S1 = S1;
-    a.dmax = dmax;
-    a.norms = norms;
-    const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(2048, (a.n4 + kBlock - 1) / kBlock));
-    hipLaunchKernelGGL(k_vap_norms, dim3(static_cast<unsigned>(grid)), dim3(kBlock), 0, h->stream, a);
-    HIP_TRY(h, hipGetLastError());
-  }
-  const double bound = h->v0 / std::sqrt(static_cast<double>(c + 1));
-  hipLaunchKernelGGL(k_vap_pick, dim3(1), dim3(64), 0, h->stream, norms, dmax, bound, c, S1, h->vap_slot, h->vap_v);
+  VapArgs a{};
+  a.ring = h->ring;
+  a.slot_stride = (h->N + h->M) * h->Kp;
+  a.n4 = a.slot_stride / 4;
+  a.c = c;
+  a.S1 = S1;
+  a.dmax = dmax;
+  a.norms = norms;
+  a.bound = h->v0 / std::sqrt(static_cast<double>(c + 1));
+  a.slot = h->vap_slot;
+  a.vlog = h->vap_v;
+  a.arrived = h->vap_arrived;
+  const dim3 grid(static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>(kVapBlocks, (a.n4 + kBlock - 1) / kBlock))));
+  if (dmax == 0) hipLaunchKernelGGL(k_vap_pick, dim3(1), dim3(64), 0, h->stream, a);
+  else if (dmax == 1) hipLaunchKernelGGL(k_vap_norms<1>, grid, dim3(kBlock), 0, h->stream, a);
+  else if (dmax == 2) hipLaunchKernelGGL(k_vap_norms<2>, grid, dim3(kBlock), 0, h->stream, a);
+  else if (dmax <= 4) hipLaunchKernelGGL(k_vap_norms<4>, grid, dim3(kBlock), 0, h->stream, a);
+  else hipLaunchKernelGGL(k_vap_norms<8>, grid, dim3(kBlock), 0, h->stream, a);
   HIP_TRY(h, hipGetLastError());
   *cls_slot = h->vap_slot;
   return PS_MF_OK;
@@ -2970,7 +2987,8 @@ int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const flo
   if ((r = upload(h, &h->slot_table, table))) return undo(r);
   if ((r = upload(h, &h->wcls, h->cls_of_worker))) return undo(r);
   if (h->policy == PS_MF_VAP &&
-      ((r = upload(h, &h->vap_slot, std::vector<int32_t>(1, 0))) || (r = vap_reserve(h, 0))))
+      ((r = upload(h, &h->vap_slot, std::vector<int32_t>(1, 0))) ||
+       (r = upload(h, &h->vap_arrived, std::vector<unsigned>(1, 0u))) || (r = vap_reserve(h, 0))))
     return undo(r);
   if (seq) {
     // the users' rows between their runs and every worker's copy of the item rows
