@@ -157,8 +157,16 @@ struct TokenRows {
 // dword access): a 32-bit lane offset (the topic) plus a 32-bit uniform offset (the row), so
 // that a row's address costs one scalar multiply; the host picks it when every such table
 // is under 2^31 bytes.  The flat form takes 64-bit row offsets for larger tables.
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 template <bool Buf>
 struct Table;
+
+// A lane's topics of a row move by one instruction where they are all below K or all past it
+// (K a multiple of the topics per lane): 7 vector memory instructions a token instead of 10 at
+// two topics a lane, 14.43 -> 14.06 ms per clock (3.9M tokens in 2 blocks, K = 100, P = 64).
+template <int KPL>
+constexpr bool wide_lanes(bool whole) { return whole && (KPL == 2 || KPL == 4); }
 
 template <>
 struct Table<true> {
@@ -172,6 +180,26 @@ struct Table<true> {
   }
   __device__ __forceinline__ int ld(Off row_off) const {
     return static_cast<int>(__builtin_amdgcn_raw_buffer_load_b32(rs, 0, static_cast<int>(row_off), 0));
+  }
+  // N consecutive counts by one instruction
+  __device__ __forceinline__ void ld_all(int (&d)[2], uint32_t lane_off, Off row_off) const {
+    const auto t = __builtin_amdgcn_raw_buffer_load_b64(rs, static_cast<int>(lane_off), static_cast<int>(row_off), 0);
+    d[0] = static_cast<int>(t[0]);
+    d[1] = static_cast<int>(t[1]);
+  }
+  __device__ __forceinline__ void ld_all(int (&d)[4], uint32_t lane_off, Off row_off) const {
+    const auto t = __builtin_amdgcn_raw_buffer_load_b128(rs, static_cast<int>(lane_off), static_cast<int>(row_off), 0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) d[j] = static_cast<int>(t[j]);
+  }
+  __device__ __forceinline__ void st_all_if(bool keep, const int (&d)[2], uint32_t lane_off, Off row_off) const {
+    __builtin_amdgcn_raw_buffer_store_b64(u32x2{static_cast<uint32_t>(d[0]), static_cast<uint32_t>(d[1])}, rs,
+                                          static_cast<int>(keep ? lane_off : 0x80000000u), static_cast<int>(row_off), 0);
+  }
+  __device__ __forceinline__ void st_all_if(bool keep, const int (&d)[4], uint32_t lane_off, Off row_off) const {
+    __builtin_amdgcn_raw_buffer_store_b128(u32x4{static_cast<uint32_t>(d[0]), static_cast<uint32_t>(d[1]),
+                                                 static_cast<uint32_t>(d[2]), static_cast<uint32_t>(d[3])}, rs,
+                                           static_cast<int>(keep ? lane_off : 0x80000000u), static_cast<int>(row_off), 0);
   }
   __device__ __forceinline__ void st(int v, uint32_t lane_off, Off row_off) const {
     __builtin_amdgcn_raw_buffer_store_b32(static_cast<uint32_t>(v), rs, static_cast<int>(lane_off), static_cast<int>(row_off), 0);
@@ -196,6 +224,21 @@ struct Table<false> {
     return *reinterpret_cast<const int32_t *>(base + row_off + lane_off);
   }
   __device__ __forceinline__ int ld(Off row_off) const { return *reinterpret_cast<const int32_t *>(base + row_off); }
+  template <int N>
+  __device__ __forceinline__ void ld_all(int (&d)[N], uint32_t lane_off, Off row_off) const {
+    typedef int V __attribute__((ext_vector_type(N), aligned(4)));
+    const V t = *reinterpret_cast<const V *>(base + row_off + lane_off);
+#pragma unroll
+    for (int j = 0; j < N; ++j) d[j] = t[j];
+  }
+  template <int N>
+  __device__ __forceinline__ void st_all_if(bool keep, const int (&d)[N], uint32_t lane_off, Off row_off) const {
+    typedef int V __attribute__((ext_vector_type(N), aligned(4)));
+    V t;
+#pragma unroll
+    for (int j = 0; j < N; ++j) t[j] = d[j];
+    if (keep) *reinterpret_cast<V *>(base + row_off + lane_off) = t;
+  }
   __device__ __forceinline__ void st(int v, uint32_t lane_off, Off row_off) const {
     *reinterpret_cast<int32_t *>(base + row_off + lane_off) = v;
   }
@@ -208,17 +251,22 @@ struct Table<false> {
 // koff[j]: the byte offset of this lane's topic j in a row (lanes past the last topic
 // re-read topic K-1: every load is issued on every path, so the waits before a use count
 // exactly; their values are masked); rb: the word's row offset in bytes
-template <int KPL, bool Buf>
+template <int KPL, bool Buf, bool Whole>
 __device__ __forceinline__ void fetch_rows(const Table<Buf> &view, const Table<Buf> &mydelta, const Table<Buf> &mytag,
                                            const Table<Buf> &z, const uint32_t (&koff)[KPL],
                                            typename Table<Buf>::Off rb, int w, int i, TokenRows<KPL> &o) {
   using Off = typename Table<Buf>::Off;
   o.tag = mytag.ld(Off{4} * static_cast<uint32_t>(w));
   o.z = z.ld(Off{4} * static_cast<uint32_t>(i));
+  if constexpr (wide_lanes<KPL>(Whole)) {
+    view.ld_all(o.nw, koff[0], rb);
+    mydelta.ld_all(o.dw, koff[0], rb);
+  } else {
 #pragma unroll
-  for (int j = 0; j < KPL; ++j) {
-    o.nw[j] = view.ld(koff[j], rb);
-    o.dw[j] = mydelta.ld(koff[j], rb);
+    for (int j = 0; j < KPL; ++j) {
+      o.nw[j] = view.ld(koff[j], rb);
+      o.dw[j] = mydelta.ld(koff[j], rb);
+    }
   }
 }
 
@@ -254,7 +302,7 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 constexpr int kDist = 3;
 constexpr int kRecStep = (64 - kDist) / (kDist + 1) * (kDist + 1);  // a multiple of the rotation, at most 64 - kDist
 
-template <int KPL, bool Buf>
+template <int KPL, bool Buf, bool Whole>
 __global__ __launch_bounds__(kWave) void k_lda_sweep(SweepArgs a) {
   using Off = typename Table<Buf>::Off;
   constexpr int R = kDist + 1;  // ring entries
@@ -282,13 +330,19 @@ __global__ __launch_bounds__(kWave) void k_lda_sweep(SweepArgs a) {
   const uint64_t rbase = a.seed ^ kDrawSalt ^ (static_cast<uint64_t>(c) << 40);
   uint32_t koff[KPL];
 #pragma unroll
-  for (int j = 0; j < KPL; ++j) koff[j] = 4u * static_cast<uint32_t>(min(lane * KPL + j, K - 1));
+  for (int j = 0; j < KPL; ++j)  // Whole: the last lane's topics again, in order
+    koff[j] = 4u * static_cast<uint32_t>(Whole ? min(lane * KPL, K - KPL) + j : min(lane * KPL + j, K - 1));
 
-  // alpha per topic slot, 0 past the last topic: there the document count is 0 as well, so
-  // the weight's numerator and the weight are 0 (the denominator is at least V beta)
-  double alpha_k[KPL];
+  // alpha and V beta per topic slot.  Past the last topic alpha is 0: there the document count
+  // is 0 as well, so the weight's numerator and the weight are 0; and V beta is 2^1000, which puts
+  // the slot's exponent difference below every topic's (their numerators and denominators lie
+  // in [2^-700, 2^700]).
+  double alpha_k[KPL], vbeta_k[KPL];
 #pragma unroll
-  for (int j = 0; j < KPL; ++j) alpha_k[j] = lane * KPL + j < K ? a.alpha : 0.0;
+  for (int j = 0; j < KPL; ++j) {
+    alpha_k[j] = lane * KPL + j < K ? a.alpha : 0.0;
+    vbeta_k[j] = lane * KPL + j < K ? a.Vbeta : 0x1p1000;
+  }
   // topic totals: the view's, and the current ones (the view's plus this worker's changes)
   int vk[KPL], nk[KPL], nd[KPL];
 #pragma unroll
@@ -310,7 +364,7 @@ __global__ __launch_bounds__(kWave) void k_lda_sweep(SweepArgs a) {
 #pragma unroll
   for (int i = 0; i < kDist; ++i) {
     const int wi = field(i, 0);
-    fetch_rows<KPL, Buf>(view, mydelta, mytag, z, koff, rowb * static_cast<Off>(wi), wi, i, rows[i]);
+    fetch_rows<KPL, Buf, Whole>(view, mydelta, mytag, z, koff, rowb * static_cast<Off>(wi), wi, i, rows[i]);
     __builtin_amdgcn_sched_barrier(0);
   }
   // the last F tokens' words (-1: none), row validity and updated own-change rows, latest first
@@ -381,13 +435,16 @@ __global__ __launch_bounds__(kWave) void k_lda_sweep(SweepArgs a) {
     }
     // the collapsed conditional's weights p_k = num_k / den_k in fp64 and the exponent of
     // the largest (computed on every lane, without a branch: lanes past the last topic hold
-    // topic K-1's rows, a zero document count and alpha = 0, so their weights are 0, and
-    // their exponents are masked).
-    // * The exponent is found without waiting for the divisions: with frexp exponents (x =
-    //   m 2^e, m in [0.5, 1)) num / den lies in [2^(e_num - e_den - 1), 2^(e_num - e_den + 1))
-    //   and never rounds up to the upper end, so the largest weight's frexp exponent is the
-    //   wavefront maximum E of e_num - e_den + 1 over the topics, or E - 1; it is E exactly
-    //   when some weight reaches 2^(E - 1).
+    // topic K-1's rows, a zero document count and alpha = 0, so their weights are 0, and their
+    // exponents are the lowest).
+    // * The exponent is found without waiting for the divisions: with the high words h of num
+    //   and den (sign 0, 11 exponent bits, 20 of the mantissa), f = floor((h_num - h_den) /
+    //   2^20) is the exponent of num / den, or one more than it where the 20 bits agree: with
+    //   mantissas a and b, num / den lies in [2^f, 2^(f + 1)) when a's 20 bits are the larger or
+    //   the smaller, and above 2^f (1 - 2^-20) when they agree, and never rounds up to 2^(f + 1).
+    //   So the largest weight's exponent is the maximum F of f, or F - 1; it is F exactly when
+    //   some weight reaches 2^F (its high word reaches (F + 1023) 2^20).  The division by 2^20
+    //   waits until the maximum of the differences is known.
     // * The divisions are the hardware reciprocal, two Newton steps, the product and one
     //   correction: the instructions the compiler emits for a correctly rounded fp64
     //   division, without its range scaling (v_div_scale) and special-case fixup
@@ -399,7 +456,7 @@ __global__ __launch_bounds__(kWave) void k_lda_sweep(SweepArgs a) {
     //   divisions, pinned by scheduling barriers: the two instructions between steps are
     //   the wait states a DPP read needs.
     double num[KPL], den[KPL], rcp[KPL], err[KPL], pk[KPL];
-    int ex = -4096;  // the lane's largest e_num - e_den; below every exponent past the last topic
+    int ex = 0;  // the lane's largest h_num - h_den
 #pragma unroll
     for (int j = 0; j < KPL; ++j) {
       const int k = lane * KPL + j;
@@ -408,10 +465,9 @@ __global__ __launch_bounds__(kWave) void k_lda_sweep(SweepArgs a) {
       const int nwx = max(rows[C].nw[j] + dw[j] - self, 0);
       const int nkx = max(nk[j] - self, 0);
       num[j] = (static_cast<double>(ndx) + alpha_k[j]) * (static_cast<double>(nwx) + a.beta);
-      den[j] = static_cast<double>(nkx) + a.Vbeta;
-      const int e = __builtin_amdgcn_frexp_exp(num[j]) - __builtin_amdgcn_frexp_exp(den[j]);
-      if (j == 0) ex = k < K ? e : -4096;
-      else if (k < K) ex = max(ex, e);
+      den[j] = static_cast<double>(nkx) + vbeta_k[j];
+      const int e = __double2hiint(num[j]) - __double2hiint(den[j]);
+      ex = j == 0 ? e : max(ex, e);
       rcp[j] = __builtin_amdgcn_rcp(den[j]);
     }
     // between two steps: the KPL operations of one Newton step
@@ -448,15 +504,15 @@ __global__ __launch_bounds__(kWave) void k_lda_sweep(SweepArgs a) {
     for (int j = 0; j < KPL; ++j) err[j] = fma(-den[j], pk[j], num[j]);
     __builtin_amdgcn_sched_barrier(0);
 #undef PS_LDA_GAP
-    const int ehi = __builtin_amdgcn_readlane(ex, 63) + 1;  // the KPL corrections before it: its wait state
+    const int ehi = __builtin_amdgcn_readlane(ex, 63) >> 20;  // the KPL corrections before it: its wait state
     int top = 0;
 #pragma unroll
     for (int j = 0; j < KPL; ++j) {
       pk[j] = fma(err[j], rcp[j], pk[j]);  // 0 past the last topic
-      top |= pk[j] >= ldexp(1.0, ehi - 1);
+      top = max(top, __double2hiint(pk[j]));
     }
     // the largest p_k lies in [2^emax, 2^(emax + 1))
-    const int emax = (__ballot(top) != 0 ? ehi : ehi - 1) - 1;
+    const int emax = __ballot(top >= (ehi + 1023) << 20) != 0 ? ehi : ehi - 1;
     // integer weights floor(p_k 2^(shift0 - emax)) (the scaling is exact), prefix sums in
     // topic order
     const int shift = a.shift0 - emax;
@@ -464,25 +520,33 @@ __global__ __launch_bounds__(kWave) void k_lda_sweep(SweepArgs a) {
     uint64_t acc = 0;
 #pragma unroll
     for (int j = 0; j < KPL; ++j) {
-      acc += static_cast<uint64_t>(floor(ldexp(pk[j], shift)));  // pk = 0 past the last topic
+      // floor(p 2^shift) in two 32-bit halves: y = p 2^(shift - 32) is below 2^31, its conversion
+      // truncates, its fraction is exact (a y too small for a normal number floors to 0 either
+      // way).  Five instructions; the conversion to 64 bits takes seven, all on the token's chain
+      // (15.29 -> 14.45 ms per clock, 3.9M tokens in 2 blocks, K = 100, P = 64).
+      const double y = ldexp(pk[j], shift - 32);  // 0 past the last topic
+      const uint32_t hi = static_cast<uint32_t>(y);
+      const uint32_t lo = static_cast<uint32_t>(ldexp(__builtin_amdgcn_fract(y), 32));
+      acc += (static_cast<uint64_t>(hi) << 32) | lo;
       loc[j] = acc;
     }
     uint64_t total;
     const uint64_t excl = wave_scan(acc, &total) - acc;
-    int k1 = k0;
-    if (total != 0) {  // always: the largest weight is at least 2^shift0
-      const uint64_t target = umulhi64_vec(ru, total);
-      const uint64_t m = __ballot(excl + acc > target);
-      const int L = __ffsll(static_cast<unsigned long long>(m)) - 1;  // m != 0: the last lane's sum is the total
-      int jj = KPL - 1;
+    // the total is at least the largest weight, 2^shift0
+    const uint64_t target = umulhi64_vec(ru, total);
+    const uint64_t m = __ballot(excl + acc > target);
+    const int L = __builtin_ctzll(m);  // m != 0: the last lane's sum is the total
+    int jj = KPL - 1;
 #pragma unroll
-      for (int j = KPL - 1; j >= 0; --j)
-        if (excl + loc[j] > target) jj = j;
-      k1 = __builtin_amdgcn_readlane(lane * KPL + jj, L);
-    }
-    const bool changed = k1 != k0;
+    for (int j = KPL - 1; j >= 0; --j)
+      if (excl + loc[j] > target) jj = j;
+    const int k1 = __builtin_amdgcn_readlane(lane * KPL + jj, L);
+    // 1 when the topic changed, formed on the scalar unit
+    int changed;
+    asm("s_cmp_lg_u32 %1, %2\n\ts_cselect_b32 %0, 1, 0" : "=s"(changed) : "s"(k1), "s"(k0) : "scc");
     if (changed) {
       const Off rb = rowb * static_cast<Off>(w);
+      bool any = !valid;  // Whole: some topic of the lane changed, or the row is all new
 #pragma unroll
       for (int j = 0; j < KPL; ++j) {
         const int k = lane * KPL + j;
@@ -490,8 +554,10 @@ __global__ __launch_bounds__(kWave) void k_lda_sweep(SweepArgs a) {
         nd[j] += dl;
         nk[j] += dl;
         dw[j] += dl;
-        mydelta.st_if(k < K && (!valid || dl != 0), dw[j], koff[j], rb);
+        any = any || dl != 0;
+        if constexpr (!wide_lanes<KPL>(Whole)) mydelta.st_if(k < K && (!valid || dl != 0), dw[j], koff[j], rb);
       }
+      if constexpr (wide_lanes<KPL>(Whole)) mydelta.st_all_if(lane * KPL < K && any, dw, koff[0], rb);
       // lane 0 stores the new topic, and the row's clock tag when the row was of an older clock
       z.st_if(lane == 0, k1, 0u, Off{4} * static_cast<uint32_t>(i));
       mytag.st_if(lane == 0 && !valid, a.tagc, 0u, Off{4} * static_cast<uint32_t>(w));
@@ -506,12 +572,12 @@ __global__ __launch_bounds__(kWave) void k_lda_sweep(SweepArgs a) {
     }
     if constexpr (F > 0) {
       fw[0] = w;
-      fvalid[0] = valid | static_cast<int>(changed);
+      fvalid[0] = valid | changed;
 #pragma unroll
       for (int j = 0; j < KPL; ++j) fdw[0][j] = dw[j];
     }
     constexpr int NF = (C + kDist) % R;
-    fetch_rows<KPL, Buf>(view, mydelta, mytag, z, koff, rowb * static_cast<Off>(wf), wf, i + kDist, rows[NF]);
+    fetch_rows<KPL, Buf, Whole>(view, mydelta, mytag, z, koff, rowb * static_cast<Off>(wf), wf, i + kDist, rows[NF]);
   };
   // whole rotations without an exit inside (an exit path would join the loop's back edge
   // with its latest fetch still in flight, and the wait at the top of the loop would then
@@ -774,8 +840,15 @@ int64_t slot_stride(const ps_lda_t *h) { return (h->V + 1) * h->K; }
 
 template <int KPL>
 void launch_sweep(const SweepArgs &a, int P, bool flat, hipStream_t st) {
-  if (flat) hipLaunchKernelGGL((k_lda_sweep<KPL, false>), dim3(P), dim3(kWave), 0, st, a);
-  else hipLaunchKernelGGL((k_lda_sweep<KPL, true>), dim3(P), dim3(kWave), 0, st, a);
+  if (wide_lanes<KPL>(true) && a.K % KPL == 0) {
+    constexpr bool W = wide_lanes<KPL>(true);
+    if (flat) hipLaunchKernelGGL((k_lda_sweep<KPL, false, W>), dim3(P), dim3(kWave), 0, st, a);
+    else hipLaunchKernelGGL((k_lda_sweep<KPL, true, W>), dim3(P), dim3(kWave), 0, st, a);
+  } else if (flat) {
+    hipLaunchKernelGGL((k_lda_sweep<KPL, false, false>), dim3(P), dim3(kWave), 0, st, a);
+  } else {
+    hipLaunchKernelGGL((k_lda_sweep<KPL, true, false>), dim3(P), dim3(kWave), 0, st, a);
+  }
 }
 
 template <int KPL>
