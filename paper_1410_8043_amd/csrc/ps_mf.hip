@@ -2812,7 +2812,8 @@ int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const flo
   lp.tile_rows_item = h->item_tile_bytes > 0
                           ? std::max<int64_t>(64, h->item_tile_bytes / (static_cast<int64_t>(h->Kp) * 4))
                           : 4 * lp.tile_rows_user;
-  lp.unit_max = h->unit_max > 0 ? h->unit_max : auto_unit_max(n / h->B);
+  // with the cells switched off by hand the split is the caller's, and units are as long as documented
+  lp.unit_max = h->unit_max > 0 ? h->unit_max : h->cells ? auto_unit_max(n / h->B) : 256;
   // The automatic split sends ratings to dense tiles and LDS cells only when the minibatch
   // blocks are large: both pay fixed costs (a partial row per cell row, workgroups that
   // each sweep a few steps) that a small block does not amortize.  Measured on the
@@ -3099,7 +3100,7 @@ int ps_mf_set_factors(ps_mf_t *h, const float *L, const float *R) {
   const size_t slot = static_cast<size_t>((h->N + h->M) * h->Kp);
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   HIP_TRY(h, hipMemset(h->ring, 0, slot * (h->s + 1) * sizeof(float)));
-  HIP_TRY(h, hipDeviceSynchronize());
+  HIP_TRY(h, hipStreamSynchronize(nullptr));  // the fill, before kernels of the handle's own stream write rows
   if ((r = rows_from_host(h, L, h->N, h->ring)) || (r = rows_from_host(h, R, h->M, h->ring + h->N * h->Kp))) return r;
   if (per_row_policy(h)) {
     // no row cached yet (version -1); slots 0 keep every address inside the ring

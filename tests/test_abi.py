@@ -455,3 +455,23 @@ def test_automatic_split_uses_dense_tiles_and_cells_only_on_large_blocks():
             assert split[0] > 0 and split[1] > 0 and split[2] > 0, split
         else:
             assert split[0] == 0 and split[1] == 0 and split[2] == w.nnz, split
+
+
+@pytest.mark.parametrize("nnz, B, longest", [(200_000, 1, 32), (600_000, 1, 64), (600_000, 4, 32)])
+def test_automatic_unit_length_follows_the_blocks(nnz, B, longest):
+    """Without options, units are cut at 32 ratings in blocks below 2^18 ratings, at 64 below 1.5
+    million; with the cells switched off by hand they keep the documented 256.  Users of
+    250 ratings are cut differently by each, which the exported counts show."""
+    from paper_1410_8043_amd import ps_mf as m
+
+    N, M = nnz // 250, 1000
+    rng = np.random.default_rng(nnz)
+    i = np.concatenate([rng.choice(M, 250, replace=False) for _ in range(N)]).astype(np.int32)
+    u = np.repeat(np.arange(N, dtype=np.int32), 250)
+    v = np.ones(u.size, np.float32)
+    units = []
+    for more in ({}, {"unit_max": longest}, {"cells": 0}, {"cells": 0, "unit_max": 256}):
+        with m.PsMf(N, M, 16, 4, 1, 0.01, 0.05, B=B, mb_seed=3, host_only=True, **more) as g:
+            g.load_ratings(u, i, v)
+            units.append([int(x) for x in g.export_index(m.IDX_SPLIT)])
+    assert units[0] == units[1] and units[2] == units[3] and units[0] != units[2], units
