@@ -970,9 +970,9 @@ struct FinalArgs {
 // without a rating in the block keep L^c_i (copied when the new slot differs).  One
 // thread per 4 columns.
 __device__ __forceinline__ void finalize_users(const FinalArgs &a, int64_t idx) {
-  const int64_t q4 = a.Kp / 4;
-  if (idx >= a.users * q4) return;
-  const int64_t i = idx / q4;
+  const int q4 = a.Kp / 4;  // a power of two
+  const int64_t i = idx >> __builtin_ctz(q4);
+  if (i >= a.users) return;
   float4 *ring4 = reinterpret_cast<float4 *>(a.ring);
   const int64_t ss4 = a.slot_stride / 4;
   // what depends on i alone is loaded at once, so that the row's chain of dependent loads
@@ -1015,19 +1015,99 @@ struct CommitArgs {
   const int32_t *cls_slot;    // [nclass]
   const float *partial;       // item-major partial rows
   const int64_t *item_pp;     // [items + 1]
+  const int32_t *many;        // the items of more than few_rows(Kp) partial rows
   float eta, lambda;
   int32_t rowmean;
   const int32_t *rs_i;        // per-row policies: [nclass * items] ring slot of each class's view of an item row
 };
 
+// four classes' view rows of an item from class q0 on; a class without a rating of the item
+// reads the current row instead and adds nothing
+struct ClassRows {
+  int cnt[4];
+  float4 r[4];
+};
+__device__ __forceinline__ ClassRows load_classes(const CommitArgs &a, const float4 *R4, int64_t j, int64_t idx, int q0) {
+  ClassRows c;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) c.cnt[u] = q0 + u < a.nclass ? a.icount_cls[j * a.nclass + q0 + u] : 0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int64_t slot = c.cnt[u] ? (a.rs_i ? a.rs_i[(q0 + u) * a.items + j] : a.cls_slot[q0 + u]) : a.slot_c;
+    c.r[u] = R4[slot * (a.slot_stride / 4) + idx];
+  }
+  return c;
+}
+// summed in class order
+__device__ __forceinline__ void add_classes(float4 &lam, const ClassRows &v) {
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if (v.cnt[u]) {
+      const float c = static_cast<float>(v.cnt[u]);
+      lam = make_float4(fmaf(c, v.r[u].x, lam.x), fmaf(c, v.r[u].y, lam.y), fmaf(c, v.r[u].z, lam.z),
+                        fmaf(c, v.r[u].w, lam.w));
+    }
+  }
+}
+__device__ __forceinline__ float4 item_row(const CommitArgs &a, int n, float4 rc, float4 d, float4 lam) {
+  const float sc = a.rowmean ? a.eta / static_cast<float>(n) : a.eta;
+  return make_float4(rc.x + sc * (d.x - a.lambda * lam.x), rc.y + sc * (d.y - a.lambda * lam.y),
+                     rc.z + sc * (d.z - a.lambda * lam.z), rc.w + sc * (d.w - a.lambda * lam.w));
+}
+
+// The items of at most few_rows(Kp) partial rows (those without a rating among them), one thread
+// per 4 columns: nothing but the row's own loads, in two levels.  A workgroup per item left most
+// of its threads without a row and waited for LDS and the classes' views after the partial rows.
+// At Kp = 256 and 512 a workgroup has 4 and 2 rows in flight of an item's and leaves few threads idle:
+// there only the items without a rating are taken.  The sums are those of commit_item to the
+// bit (it has 8 row lanes or more up to Kp = 128, so each adds one row).
+// k_commit, a workgroup for each item / this, us a clock: 70,000 + 14,000 rows at K = 64, 1.2M ratings
+// 28.7 / 17.9; 30,000 + 6000 at K = 64 with a version per row 14.5 / 11.2; 12,345 + 6789 at Kp = 128 12.9 /
+// 10.1; 1000 + 500 at K = 16 5.9 / 4.0; 60,007 + 10,007 at K = 128, nearly all items of many
+// rows, 49.7 / 51.2.  At Kp = 256 with 8 here too: 40.9 / 45.6.  (The users' workgroups last: 21.4, 12.2, 11.4.)
+__host__ __device__ constexpr int few_rows(int Kp) { return Kp <= 128 ? 8 : 0; }
+__device__ __forceinline__ void commit_item_few(const CommitArgs &a, int64_t idx) {
+  const int q4 = a.Kp / 4;  // a power of two
+  const int64_t j = idx >> __builtin_ctz(q4);
+  if (j >= a.items) return;
+  float4 *R4 = reinterpret_cast<float4 *>(a.ring + a.r_off);
+  const int64_t ss4 = a.slot_stride / 4;
+  const int n = a.icount[j];
+  const int64_t p0 = a.item_pp[j], p1 = a.item_pp[j + 1];
+  if (p1 - p0 > few_rows(a.Kp)) return;  // in the list of the others
+  const float4 rc = R4[a.slot_c * ss4 + idx];
+  if (n == 0) {
+    if (a.slot_n != a.slot_c) R4[a.slot_n * ss4 + idx] = rc;
+    return;
+  }
+  ClassRows v = load_classes(a, R4, j, idx, 0);
+  const f32x4 *part4 = reinterpret_cast<const f32x4 *>(a.partial) + (idx - j * q4);
+  float4 d = make_float4(0.f, 0.f, 0.f, 0.f), lam = d;
+  for (int64_t p = p0; p < p1; p += 4) {
+    f32x4 t[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[u] = ld_partial(part4 + min(p + u, p1 - 1) * q4);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (p + u < p1) { d.x += t[u][0]; d.y += t[u][1]; d.z += t[u][2]; d.w += t[u][3]; }
+    }
+  }
+  add_classes(lam, v);
+  for (int q0 = 4; q0 < a.nclass; q0 += 4) {
+    v = load_classes(a, R4, j, idx, q0);
+    add_classes(lam, v);
+  }
+  R4[a.slot_n * ss4 + idx] = item_row(a, n, rc, d, lam);
+}
+
 // R^{c+1}_j = R^c_j + scale_j (sum of j's partial rows - lambda sum_class n_j^(class) R^{v(class)}_j).
-// One workgroup per item: thread t sums the float4 column t mod (Kp/4) of every
+// One workgroup per item of more than few_rows(Kp) partial rows: thread t sums the float4 column t mod (Kp/4) of every
 // (kBlock / (Kp/4))-th partial row, starting at row t / (Kp/4); the column sums are then
 // added in row-lane order through LDS (popular items own thousands of partial rows).
 __device__ __forceinline__ void commit_item(const CommitArgs &a, int64_t j, float4 *red) {
   const int q4 = a.Kp / 4;
   const int lanes = kBlock / q4;  // row lanes: Kp is a power of two in [8, 512], so 2..128
-  const int k4 = static_cast<int>(threadIdx.x) % q4, lane = static_cast<int>(threadIdx.x) / q4;
+  const int k4 = static_cast<int>(threadIdx.x) & (q4 - 1), lane = static_cast<int>(threadIdx.x) >> __builtin_ctz(q4);
   float4 *R4 = reinterpret_cast<float4 *>(a.ring + a.r_off);
   const int64_t ss4 = a.slot_stride / 4;
   const int64_t idx = j * q4 + k4;
@@ -1035,10 +1115,6 @@ __device__ __forceinline__ void commit_item(const CommitArgs &a, int64_t j, floa
   const int64_t p0 = a.item_pp[j], p1 = a.item_pp[j + 1];
   float4 rc = make_float4(0.f, 0.f, 0.f, 0.f);
   if (lane == 0) rc = R4[a.slot_c * ss4 + idx];  // loaded before the partial rows
-  if (n == 0) {  // uniform over the workgroup
-    if (lane == 0) R4[a.slot_n * ss4 + idx] = rc;
-    return;
-  }
   float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
   const f32x4 *part4 = reinterpret_cast<const f32x4 *>(a.partial);
 #pragma unroll 4
@@ -1053,31 +1129,9 @@ __device__ __forceinline__ void commit_item(const CommitArgs &a, int64_t j, floa
     const float4 t = red[l * q4 + k4];
     d.x += t.x; d.y += t.y; d.z += t.z; d.w += t.w;
   }
-  // the classes' view rows, four classes' loads at a time (a class without a rating of the
-  // item reads the current row instead and adds nothing), summed in class order
   float4 lam = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int q0 = 0; q0 < a.nclass; q0 += 4) {
-    int cnt[4];
-    float4 r[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) cnt[u] = q0 + u < a.nclass ? a.icount_cls[j * a.nclass + q0 + u] : 0;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t slot = cnt[u] ? (a.rs_i ? a.rs_i[(q0 + u) * a.items + j] : a.cls_slot[q0 + u]) : a.slot_c;
-      r[u] = R4[slot * ss4 + idx];
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (cnt[u]) {
-        const float c = static_cast<float>(cnt[u]);
-        lam = make_float4(fmaf(c, r[u].x, lam.x), fmaf(c, r[u].y, lam.y), fmaf(c, r[u].z, lam.z),
-                          fmaf(c, r[u].w, lam.w));
-      }
-    }
-  }
-  const float sc = a.rowmean ? a.eta / static_cast<float>(n) : a.eta;
-  R4[a.slot_n * ss4 + idx] = make_float4(rc.x + sc * (d.x - a.lambda * lam.x), rc.y + sc * (d.y - a.lambda * lam.y),
-                                         rc.z + sc * (d.z - a.lambda * lam.z), rc.w + sc * (d.w - a.lambda * lam.w));
+  for (int q0 = 0; q0 < a.nclass; q0 += 4) add_classes(lam, load_classes(a, R4, j, idx, q0));
+  R4[a.slot_n * ss4 + idx] = item_row(a, n, rc, d, lam);
 }
 
 // ------------------------------------------------------------------ per-row views
@@ -1133,15 +1187,19 @@ __global__ __launch_bounds__(kBlock) void k_row_views(RowViewArgs a) {
     if (hist[t]) atomicAdd(a.stale + t, hist[t]);
 }
 
-// Version c+1 of both factors in one launch: workgroups [0, grid_users) finalize L (one
-// thread per 4 columns of a user), the rest commit R (one workgroup per item).  They write
-// different rows of the new slot and read only partial rows and versions <= c.
-__global__ __launch_bounds__(kBlock) void k_commit(FinalArgs fa, CommitArgs ca, int32_t grid_users) {
+// Version c+1 of both factors in one launch: workgroups [0, grid_users) finalize L, the next
+// nmany commit an item of many partial rows each and the rest the other items, one thread
+// per 4 columns of a row for L and those.  They write different rows of the new slot and read
+// only partial rows and versions <= c.
+__global__ __launch_bounds__(kBlock) void k_commit(FinalArgs fa, CommitArgs ca, int32_t grid_users, int32_t nmany) {
   __shared__ float4 red[kBlock];
-  if (static_cast<int32_t>(blockIdx.x) < grid_users)
+  const int32_t b = static_cast<int32_t>(blockIdx.x) - grid_users;
+  if (b < 0)
     finalize_users(fa, static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x);
+  else if (b < nmany)
+    commit_item(ca, ca.many[b], red);
   else
-    commit_item(ca, static_cast<int64_t>(blockIdx.x) - grid_users, red);
+    commit_item_few(ca, static_cast<int64_t>(b - nmany) * kBlock + threadIdx.x);
 }
 
 // Debug check of the commit (PS_MF_OPT_POISON): before the commit of clock c, every row of
@@ -1828,6 +1886,8 @@ struct DeviceUnits {
   float *val = nullptr;
   int32_t *unit_x = nullptr, *unit_cls = nullptr, *unit_len = nullptr, *unit_out = nullptr;
   int64_t *unit_beg = nullptr, *xcd_off = nullptr, *x_pp = nullptr;
+  int32_t *x_many = nullptr;  // item-major set: the items of more than few_rows(Kp) partial rows
+  int32_t nmany = 0;
   uint8_t *sole = nullptr;  // user-major set: rows whose only partial row is one unit's
 };
 
@@ -2468,11 +2528,12 @@ int one_clock(ps_mf_t *h) {
   ca.cls_slot = cls_slot;
   ca.partial = h->partial_i;
   ca.item_pp = db.by_item.x_pp;
+  ca.many = db.by_item.x_many;
   ca.eta = eta_at(h, c);
   ca.lambda = h->lambda;
   ca.rowmean = rowmean;
   ca.rs_i = per_row_policy(h) ? h->slot_i : nullptr;
-  const int64_t grid_users = (nfin + kBlock - 1) / kBlock, grid_items = h->M;
+  const int64_t grid_users = (nfin + kBlock - 1) / kBlock, grid_few = (h->M * h->Kp / 4 + kBlock - 1) / kBlock;
   hipEvent_t ev = nullptr;
   if ((rc = record(h, &ev))) return rc;
   if (per_row_policy(h) && (rc = row_views(h, db, c))) return rc;
@@ -2589,8 +2650,9 @@ int one_clock(ps_mf_t *h) {
                        fa, ca);
     HIP_TRY(h, hipGetLastError());
   }
-  hipLaunchKernelGGL(k_commit, dim3(static_cast<unsigned>(grid_users + grid_items)), dim3(kBlock), 0, h->stream, fa,
-                     ca, static_cast<int32_t>(grid_users));
+  const int32_t nmany = db.by_item.nmany;
+  hipLaunchKernelGGL(k_commit, dim3(static_cast<unsigned>(grid_users + nmany + grid_few)), dim3(kBlock), 0, h->stream, fa,
+                     ca, static_cast<int32_t>(grid_users), nmany);
   HIP_TRY(h, hipGetLastError());
   if ((rc = record_end(h, PS_MF_KERNEL_COMMIT, ev))) return rc;
 
@@ -2923,6 +2985,12 @@ int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const flo
                (r = upload_dense(h, d.dense_user, L.dense_user, true)) ||
                (r = upload_dense(h, d.dense_item, L.dense_item, false))) {
       return undo(r);
+    } else {
+      std::vector<int32_t> many;
+      for (int64_t j = 0; j < h->M; ++j)
+        if (L.by_item.x_pp[j + 1] - L.by_item.x_pp[j] > few_rows(h->Kp)) many.push_back(static_cast<int32_t>(j));
+      d.by_item.nmany = static_cast<int32_t>(many.size());
+      if ((r = upload(h, &d.by_item.x_many, many))) return undo(r);
     }
     // partial rows of units and cells, + the row the padding units write
     max_units_u = std::max<int64_t>(max_units_u, L.partial_rows_user + 1);
