@@ -1055,11 +1055,11 @@ __device__ __forceinline__ float4 item_row(const CommitArgs &a, int n, float4 rc
                      rc.z + sc * (d.z - a.lambda * lam.z), rc.w + sc * (d.w - a.lambda * lam.w));
 }
 
-// The items of at most few_rows(Kp) partial rows (those without a rating among them), one thread
+// The items of at most few_rows(Kp) partial rows, one thread
 // per 4 columns: nothing but the row's own loads, in two levels.  A workgroup per item left most
 // of its threads without a row and waited for LDS and the classes' views after the partial rows.
 // At Kp = 256 and 512 a workgroup has 4 and 2 rows in flight of an item's and leaves few threads idle:
-// there only the items without a rating are taken.  The sums are those of commit_item to the
+// there only the items without a partial row are taken.  The sums are those of commit_item to the
 // bit (it has 8 row lanes or more up to Kp = 128, so each adds one row).
 // k_commit, a workgroup for each item / this, us a clock: 70,000 + 14,000 rows at K = 64, 1.2M ratings
 // 28.7 / 17.9; 30,000 + 6000 at K = 64 with a version per row 14.5 / 11.2; 12,345 + 6789 at Kp = 128 12.9 /
@@ -1115,6 +1115,10 @@ __device__ __forceinline__ void commit_item(const CommitArgs &a, int64_t j, floa
   const int64_t p0 = a.item_pp[j], p1 = a.item_pp[j + 1];
   float4 rc = make_float4(0.f, 0.f, 0.f, 0.f);
   if (lane == 0) rc = R4[a.slot_c * ss4 + idx];  // loaded before the partial rows
+  if (n == 0) {  // uniform over the workgroup; a dense tile gives partial rows to items without a rating too
+    if (lane == 0) R4[a.slot_n * ss4 + idx] = rc;
+    return;
+  }
   float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
   const f32x4 *part4 = reinterpret_cast<const f32x4 *>(a.partial);
 #pragma unroll 4
