@@ -112,7 +112,9 @@ typedef struct ps_mf ps_mf_t;
                                    theorems); 0 (default): constant eta */
 #define PS_MF_OPT_SEQ_GRAPHS 16 /* 1 (default): under PS_MF_STEP_SEQ, capture each clock's sub-epoch
                                    launches once per (block, view schedule) into a HIP graph on the
-                                   handle's stream and replay it (not with PS_MF_OPT_ETA_DECAY);
+                                   handle's stream and replay it (not with PS_MF_OPT_ETA_DECAY, and
+                                   not for blocks in lists, which take one launch a clock; see
+                                   PS_MF_OPT_SEQ_LISTS);
                                    0: launch them one by one */
 #define PS_MF_OPT_ITEM_TILE_BYTES 17 /* bytes of item rows per tile of the user-major sweep's work
                                         units (each tile is read from one XCD's L2); -1 (default):
@@ -139,6 +141,12 @@ typedef struct ps_mf ps_mf_t;
                                     view is not the new version's ring slot, and the commit skips
                                     it; 0 (and with PS_MF_OPT_SWEEP_GRAPHS): every user through
                                     the commit.  Same results */
+#define PS_MF_OPT_SEQ_LISTS 22 /* how PS_MF_STEP_SEQ runs a block: 0 in chains (a launch per
+                                  sub-epoch, a wavefront per chain); 1 in lists (one launch, a
+                                  workgroup of 16 wavefronts per worker, a list of its users'
+                                  ratings each), or in chains where a worker has 2^20 ratings of
+                                  the block or more; -1 (default): the form estimated faster.
+                                  Same results, bit for bit */
 
 /* Views (Section 3.2 SSP condition; Section 4 ESSPTable).  The table-level policies give
    worker p at clock c one whole version v = max(0, c - d):
@@ -207,6 +215,10 @@ typedef struct ps_mf ps_mf_t;
 #define PS_MF_IDX_VAP_NORMS 11  /* double [clocks * (s+1)] under PS_MF_VAP: entry c*(s+1) + d is the
                                    in-transit norm |x_c - x_{c-d}|_inf when clock c started
                                    (-1 where c - d < 0); other policies: PS_MF_EINVAL */
+#define PS_MF_IDX_SEQ_LISTS 12  /* int32 [16 P + 1] under PS_MF_STEP_SEQ where block b runs in lists:
+                                   list l of worker p holds entries [16 p + l] to [16 p + l + 1] of
+                                   the block's ratings in list order; length 0 where it runs in
+                                   chains or has no rating; other steps: PS_MF_EINVAL */
 
 /* kernel ids (ps_mf_kernel_time) */
 #define PS_MF_KERNEL_SWEEP 0  /* residual, dL segment-sum and dR accumulation of one clock */

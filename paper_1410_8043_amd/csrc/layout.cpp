@@ -744,7 +744,7 @@ void build_dense(const LayoutParams &p, const BlockLayout &L, const std::vector<
 void build_seq_lists(const LayoutParams &p, BlockLayout &L, const std::vector<std::vector<int64_t>> &chains_of) {
   SeqSet &S = L.seq;
   const int64_t P = p.workers, M = p.items, D = p.seq_list_ahead;
-  if (L.nnz == 0 || p.seq_list_ahead == 0) return;
+  if (L.nnz == 0 || p.seq_lists == 0) return;
   // Lists or chains, by what each was measured to take (us, MI355X):
   //   chains: a launch per sub-epoch, 4.5 and 0.33 per rating of its longest chain;
   //   lists: the most of 0.045 per rating of the busiest worker (its CU's 16 wavefronts), 0.4 per
@@ -784,7 +784,7 @@ void build_seq_lists(const LayoutParams &p, BlockLayout &L, const std::vector<st
   }
   const double t_lists = std::max({0.045 * static_cast<double>(worker_most), 0.4 * static_cast<double>(user_most),
                                    2.0 * static_cast<double>(item_most)});
-  if (t_lists >= t_chains || worker_most > kSeqListMost) return;
+  if (worker_most > kSeqListMost || (p.seq_lists < 0 && t_lists >= t_chains)) return;
   // each worker's users to its lists: the busiest user first, to the shortest list so far
   std::vector<std::vector<int32_t>> users_of(static_cast<size_t>(P));
   for (int64_t i = 0; i < p.users; ++i)

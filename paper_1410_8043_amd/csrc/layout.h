@@ -194,7 +194,9 @@ struct LayoutParams {
   int32_t min_cell_steps = 4;       // runs of cells and dense cells are not cut below this many
                                     // steps (each cut costs every row of the cell a partial row)
   int32_t workers = 1;              // P
-  int32_t seq_list_ahead = 4;       // ratings that a list's rows are fetched ahead, at most 15 (0: no lists)
+  int32_t seq_list_ahead = 4;       // ratings that a list's rows are fetched ahead, at most 15
+  int32_t seq_lists = -1;           // sequential step: 0 chains, 1 lists where the count can name every rating
+                                    // of a worker, -1 the form that is estimated faster
   int32_t seq_groups = 0;           // G > 0: build the sequential step's order (SeqSet) instead of
                                     // units, cells and dense tiles
 };

@@ -1954,6 +1954,7 @@ struct ps_mf {
   double v0 = INFINITY;          // value bound of the VAP policy
   bool eta_decay = false;        // step eta / sqrt(c + 1) at clock c
   bool seq_graphs = true;        // replay each clock's sub-epoch launches from a captured HIP graph
+  int32_t seq_lists = -1;        // sequential step: 0 chains, 1 lists (-1: the one estimated faster)
   std::vector<hipGraphExec_t> seq_exec;  // per (block, slot-table row)
   bool sweep_graphs = false;     // replay each clock's sweep launches from a captured HIP graph
   bool unit_commit = true;       // a user's only unit writes its new version (see UnitArgs::sole)
@@ -2758,6 +2759,10 @@ int ps_mf_set_option(ps_mf_t *h, int32_t key, int64_t value) {
     case PS_MF_OPT_SEQ_GRAPHS:
       h->seq_graphs = value != 0;
       return PS_MF_OK;
+    case PS_MF_OPT_SEQ_LISTS:
+      if (value < -1 || value > 1) return fail(h, PS_MF_EINVAL, "the sequential step's form must be in [-1, 1]");
+      h->seq_lists = static_cast<int32_t>(value);
+      return PS_MF_OK;
     case PS_MF_OPT_ITEM_TILE_BYTES:
       if (value < 1 && value != -1) return fail(h, PS_MF_EINVAL, "item tile bytes must be >= 1 or -1");
       h->item_tile_bytes = value;
@@ -2903,6 +2908,7 @@ int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const flo
   if (seq) {
     lp.seq_groups = h->seq_groups;
     lp.seq_list_ahead = seq_list_ahead(h->Kp / 64);
+    lp.seq_lists = h->seq_lists;
     lp.dense_min = 0;
     lp.cell_rows = lp.cell_groups = 0;
   }
@@ -3258,8 +3264,8 @@ int ps_mf_export_index(ps_mf_t *h, int32_t kind, int32_t block, void *buf, int64
     if (!h->loaded) return fail(h, PS_MF_ESTATE, "no ratings loaded");
     if (block < 0 || block >= h->B) return fail(h, PS_MF_EINVAL, "block %d out of range", block);
   }
-  if (kind == PS_MF_IDX_SEQ_ORDER && h->step != PS_MF_STEP_SEQ)
-    return fail(h, PS_MF_EINVAL, "the order of the sequential step exists under PS_MF_STEP_SEQ only");
+  if ((kind == PS_MF_IDX_SEQ_ORDER || kind == PS_MF_IDX_SEQ_LISTS) && h->step != PS_MF_STEP_SEQ)
+    return fail(h, PS_MF_EINVAL, "the order and the lists of the sequential step exist under PS_MF_STEP_SEQ only");
   if (kind == PS_MF_IDX_VAP_NORMS && h->policy != PS_MF_VAP)
     return fail(h, PS_MF_EINVAL, "in-transit norms exist under PS_MF_VAP only");
   if (kind == PS_MF_IDX_VERSION_LOG || kind == PS_MF_IDX_STALENESS) {
@@ -3356,6 +3362,9 @@ int ps_mf_export_index(ps_mf_t *h, int32_t kind, int32_t block, void *buf, int64
     case PS_MF_IDX_VERSION_LOG: src = h->vlog.data(); esz = 8; n = static_cast<int64_t>(h->vlog.size()); break;
     case PS_MF_IDX_SPLIT: src = split; esz = 8; n = 8; break;
     case PS_MF_IDX_SEQ_ORDER: src = seq_order.data(); esz = 8; n = static_cast<int64_t>(seq_order.size()); break;
+    case PS_MF_IDX_SEQ_LISTS:
+      src = h->layout[block].seq.list_beg.data(); esz = 4; n = static_cast<int64_t>(h->layout[block].seq.list_beg.size());
+      break;
     case PS_MF_IDX_VAP_NORMS: src = vap_norms.data(); esz = 8; n = static_cast<int64_t>(vap_norms.size()); break;
     default: return fail(h, PS_MF_EINVAL, "unknown index kind %d", kind);
   }

@@ -26,11 +26,11 @@ LIB_PATH = os.path.join(_HERE, "libps_mf.so")
 OK, EINVAL, ENOMEM, EDEVICE, ESTATE, EINTERNAL = 0, -1, -2, -3, -4, -5
 (OPT_POLICY, OPT_STEP, OPT_MB_BLOCKS, OPT_MB_SEED, OPT_HOST_ONLY, OPT_TIMING, OPT_TILE_BYTES, OPT_UNIT_MAX, OPT_CELLS,
  OPT_HEAVY_MIN, OPT_TWO_STREAMS, OPT_HOT_STEPS, OPT_DENSE_MIN, OPT_SEQ_STRATA, OPT_ETA_DECAY,
- OPT_SEQ_GRAPHS, OPT_ITEM_TILE_BYTES, OPT_DEVICE, OPT_POISON, OPT_SWEEP_GRAPHS, OPT_UNIT_COMMIT) = range(1, 22)
+ OPT_SEQ_GRAPHS, OPT_ITEM_TILE_BYTES, OPT_DEVICE, OPT_POISON, OPT_SWEEP_GRAPHS, OPT_UNIT_COMMIT, OPT_SEQ_LISTS) = range(1, 23)
 SSP_LAZY, SSP_WORST, ESSP, SSP_ROW, ESSP_ROW, VAP = 0, 1, 2, 3, 4, 5
 STEP_ROWMEAN, STEP_SUM, STEP_SEQ = 0, 1, 2
 (IDX_OWNER, IDX_ROW_PTR, IDX_COL, IDX_PERM, IDX_USER_COUNT, IDX_ITEM_COUNT, IDX_VERSION_LOG, IDX_SPLIT, IDX_STALENESS,
- IDX_ROW_VERSIONS, IDX_SEQ_ORDER, IDX_VAP_NORMS) = range(12)
+ IDX_ROW_VERSIONS, IDX_SEQ_ORDER, IDX_VAP_NORMS, IDX_SEQ_LISTS) = range(13)
 KERNEL_SWEEP, KERNEL_COMMIT = 0, 1
 
 SYMBOLS = ("ps_mf_create", "ps_mf_set_option", "ps_mf_set_value_bound", "ps_mf_set_owner_map", "ps_mf_set_stream",
@@ -173,7 +173,7 @@ def ps_mf_get_clock(h):
 def ps_mf_export_index(h, kind, block=0):
     n = ctypes.c_int64()
     _check(h, "ps_mf_export_index", _lib.ps_mf_export_index(h, int(kind), int(block), None, 0, ctypes.byref(n)))
-    dt = (np.int32 if kind in (IDX_OWNER, IDX_COL, IDX_USER_COUNT, IDX_ITEM_COUNT) else
+    dt = (np.int32 if kind in (IDX_OWNER, IDX_COL, IDX_USER_COUNT, IDX_ITEM_COUNT, IDX_SEQ_LISTS) else
           np.float64 if kind == IDX_VAP_NORMS else np.int64)
     buf = np.empty(n.value, dtype=dt)
     _check(h, "ps_mf_export_index", _lib.ps_mf_export_index(h, int(kind), int(block),
@@ -204,7 +204,7 @@ class PsMf:
                  owner=None, host_only=False, timing=False, stream=None, tile_bytes=None, unit_max=None,
                  cells=None, heavy_min=None, two_streams=None, hot_steps=None, dense_min=None, strata=None,
                  value_bound=None, eta_decay=False, seq_graphs=None, item_tile_bytes=None, device=None,
-                 poison=False, sweep_graphs=None, unit_commit=None):
+                 poison=False, sweep_graphs=None, unit_commit=None, seq_lists=None):
         self.N, self.M, self.K, self.P, self.s = int(users), int(items), int(K), int(P), int(s)
         self.h = ps_mf_create(users, items, K, P, s, eta, lam)
         try:
@@ -248,6 +248,8 @@ class PsMf:
                 ps_mf_set_option(self.h, OPT_SWEEP_GRAPHS, int(bool(sweep_graphs)))
             if unit_commit is not None:
                 ps_mf_set_option(self.h, OPT_UNIT_COMMIT, int(bool(unit_commit)))
+            if seq_lists is not None:
+                ps_mf_set_option(self.h, OPT_SEQ_LISTS, seq_lists)
             if owner is not None:
                 ps_mf_set_owner_map(self.h, owner)
             if stream is not None:

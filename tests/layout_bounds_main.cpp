@@ -38,7 +38,7 @@ Coo make(int64_t N, int64_t M, int64_t n, uint64_t seed, bool skew) {
 }
 
 int run(const char *name, const Coo &c, int P, int nclass, int B, int Kp, int64_t heavy_min, int hot_steps,
-        int dense_min, int unit_max, int64_t tile_rows, int seq_groups) {
+        int dense_min, int unit_max, int64_t tile_rows, int seq_groups, int seq_lists = -1) {
   std::vector<int32_t> owner(static_cast<size_t>(c.N)), cls(static_cast<size_t>(P));
   for (int64_t x = 0; x < c.N; ++x) owner[static_cast<size_t>(x)] = static_cast<int32_t>((x * 7 + 3) % P);
   for (int p = 0; p < P; ++p) cls[static_cast<size_t>(p)] = p % nclass;
@@ -57,6 +57,7 @@ int run(const char *name, const Coo &c, int P, int nclass, int B, int Kp, int64_
   lp.workers = P;
   if (seq_groups > 0) {
     lp.seq_groups = seq_groups;
+    lp.seq_lists = seq_lists;
   } else {
     lp.cell_rows = 32768 / Kp;
     lp.cell_groups = 1024 / (Kp >= 128 ? 8 : Kp >= 32 ? 8 : 4);
@@ -114,13 +115,16 @@ int main() {
         bad += run(name, *c, 4, 2, B, Kp, 30, 1, Kp >= 16 && Kp <= 256 ? 10 : 0, 256, 1 << 20, 0);
       }
       for (int G : {1, 7}) {
-        std::snprintf(name, sizeof name, "%s B=%d seq G=%d", c == &uni ? "uniform" : "skewed", B, G);
-        bad += run(name, *c, 5, 3, B, 16, 0, 0, 0, 256, 64, G);
+        for (int lists : {0, 1}) {
+          std::snprintf(name, sizeof name, "%s B=%d seq G=%d lists=%d", c == &uni ? "uniform" : "skewed", B, G, lists);
+          bad += run(name, *c, 5, 3, B, 16, 0, 0, 0, 256, 64, G, lists);
+        }
       }
     }
   }
   bad += run("one rating row", tiny, 1, 1, 1, 16, 1, 1, 1, 1, 1, 0);
-  bad += run("one rating row seq", tiny, 1, 1, 2, 16, 0, 0, 0, 1, 1, 3);
+  bad += run("one rating row seq", tiny, 1, 1, 2, 16, 0, 0, 0, 1, 1, 3, 0);
+  bad += run("one rating row seq lists", tiny, 1, 1, 2, 16, 0, 0, 0, 1, 1, 3, 1);
   bad += run("empty", empty, 3, 2, 2, 16, 1, 1, 1, 8, 8, 0);
   bad += run("empty seq", empty, 3, 2, 2, 16, 0, 0, 0, 8, 8, 4);
   std::printf("%d failures\n", bad);

@@ -35,7 +35,7 @@ def test_every_header_constant_matches_the_binding():
     policies, steps, exports, timing kinds) has the same value in the Python binding."""
     text = open(os.path.join(ROOT, "include", "ps_mf.h")).read()
     consts = dict(re.findall(r"#define PS_MF_([A-Z_0-9]+) \(?(-?\d+)\)?", text))
-    assert len(consts) == 50, len(consts)
+    assert len(consts) == 52, len(consts)
     for name, value in consts.items():
         assert getattr(ps_mf, name) == int(value), name
 
@@ -334,6 +334,45 @@ def test_seq_option_errors():
         with ps_mf.PsMf(4, 3, 2, 2, 1, 0.1, 0.1, policy=policy, step=ps_mf.STEP_SEQ, host_only=True) as g:
             g.load_ratings(np.array([0, 3]), np.array([0, 2]), np.array([1.0, 2.0]))
             assert g.export_index(ps_mf.IDX_SEQ_ORDER).size == 2
+
+
+def test_seq_form_option_and_export():
+    """Chains and lists on request: the layout's self-check passes for either form, the export
+    is empty for chains and for a block without ratings, else holds 16 lists a worker with
+    the worker's ratings; a worker of 2^20 ratings stays in chains."""
+    rng = np.random.default_rng(5)
+    N, M, P, B = 200, 60, 5, 2
+    user, item = rng.integers(0, N, 3000).astype(np.int32), rng.integers(0, M, 3000).astype(np.int32)
+    val = np.ones(3000, np.float32)
+    for lists in (0, 1):
+        with ps_mf.PsMf(N, M, 8, P, 1, 0.01, 0.05, step=ps_mf.STEP_SEQ, strata=7, B=B, mb_seed=1, host_only=True,
+                        seq_lists=lists) as g:
+            g.load_ratings(user, item, val)
+            for b in range(B):
+                beg = g.export_index(ps_mf.IDX_SEQ_LISTS, b)
+                if not lists:
+                    assert beg.size == 0
+                    continue
+                per_worker = np.bincount(np.arange(N) % P, g.export_index(ps_mf.IDX_USER_COUNT, b), P)
+                assert beg.size == 16 * P + 1 and np.array_equal(np.diff(beg[::16]), per_worker)
+    with ps_mf.PsMf(N, M, 8, P, 1, 0.01, 0.05, step=ps_mf.STEP_SEQ, host_only=True, seq_lists=1) as g:
+        g.load_ratings(user[:0], item[:0], val[:0])
+        assert g.export_index(ps_mf.IDX_SEQ_LISTS).size == 0
+    n = 1 << 20
+    for more, length in ((0, 17), (1, 0)):
+        k = np.arange(n - 1 + more)
+        with ps_mf.PsMf(2048, 2048, 8, 1, 0, 0.01, 0.05, step=ps_mf.STEP_SEQ, host_only=True, seq_lists=1) as g:
+            g.load_ratings(k // 512, k % 2048, np.ones(k.size))
+            assert g.export_index(ps_mf.IDX_SEQ_LISTS).size == length
+    with ps_mf.PsMf(N, M, 8, P, 1, 0.01, 0.05, host_only=True) as g:
+        for v in (-2, 2):
+            with pytest.raises(ps_mf.PsMfError) as e:
+                ps_mf.ps_mf_set_option(g.h, ps_mf.OPT_SEQ_LISTS, v)
+            assert e.value.code == ps_mf.EINVAL
+        g.load_ratings(user, item, val)
+        with pytest.raises(ps_mf.PsMfError) as e:
+            g.export_index(ps_mf.IDX_SEQ_LISTS)
+        assert e.value.code == ps_mf.EINVAL
 
 
 # ---------------------------------------------------------------- value-bounded views (PS_MF_VAP)

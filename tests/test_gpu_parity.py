@@ -85,6 +85,27 @@ def run_both(ps_mf, w_user, w_item, w_val, L0, R0, *, N, M, K, P, s, eta, lam, c
                 Lv, Rv = g.get_version(v)
                 Lov, Rov = o.get_version(v)
                 assert max(np.abs(Lv - Lov).max(), np.abs(Rv - Rov).max()) <= FACTOR_TOL
+    if step == oracle.SEQ:
+        # the sequential step runs a block in chains or in lists, whichever is estimated faster
+        # (above); forced into either, it gives the same bits
+        for lists in (0, 1):
+            with ps_mf.PsMf(N, M, K, P, s, eta, lam, policy=policy, step=step, B=B, mb_seed=seed, owner=owner,
+                            strata=strata, value_bound=value_bound, eta_decay=eta_decay, seq_lists=lists,
+                            **handle_opts) as g:
+                g.load_ratings(w_user, w_item, w_val)
+                for b in range(B):
+                    ratings = g.export_index(ps_mf.IDX_SPLIT, b)[2]
+                    assert g.export_index(ps_mf.IDX_SEQ_LISTS, b).size == (16 * P + 1 if lists and ratings else 0)
+                g.set_factors(L0, R0)
+                g.clock(clocks)
+                for f, (Lf, Rf) in (("latest", g.get_factors()), ("oldest", g.get_version(max(0, clocks - s)))):
+                    if f == "latest":
+                        assert np.array_equal(Lf, L) and np.array_equal(Rf, R), lists
+                        assert g.loss() == loss
+                    elif lists == 0:
+                        oldest = Lf, Rf
+                    else:
+                        assert np.array_equal(Lf, oldest[0]) and np.array_equal(Rf, oldest[1])
     return err
 
 
@@ -556,8 +577,9 @@ def test_seq_graph_replays_equal_eager_launches(gpu, policy, s, B):
     out = []
     for graphs in (True, False):
         with gpu.PsMf(N, M, K, 5, s, 0.02, 0.05, policy=policy, step=gpu.STEP_SEQ, strata=7, B=B, mb_seed=3,
-                      value_bound=0.05 if policy == oracle.VAP else None, seq_graphs=graphs) as g:
+                      value_bound=0.05 if policy == oracle.VAP else None, seq_graphs=graphs, seq_lists=0) as g:
             g.load_ratings(user, item, val)
+            assert all(g.export_index(gpu.IDX_SEQ_LISTS, b).size == 0 for b in range(B))  # chains: what the graphs hold
             g.set_factors(L0, R0)
             hist = []
             for _ in range(3 * (2 * s + 1) * B):
@@ -640,10 +662,11 @@ def test_medium_shape_scaled_seq_per_row_ragged_rank(gpu):
              lam=spec.lam, clocks=8, policy=oracle.SSP_ROW, step=oracle.SEQ, strata=32, B=spec.B, seed=spec.seed)
 
 
-def test_seq_clock_inside_a_callers_graph_capture(gpu):
+@pytest.mark.parametrize("lists", [0, 1])
+def test_seq_clock_inside_a_callers_graph_capture(gpu, lists):
     """A caller may capture a sequential clock into its own HIP graph (torch.cuda.graph on
-    the handle's stream): the library then launches the sub-epochs one by one into the
-    caller's capture.  With s = 0 and one block every clock runs the same launches, so every
+    the handle's stream): the library then launches the sub-epochs one by one (a block in
+    lists: its one launch) into the caller's capture.  With s = 0 and one block every clock runs the same launches, so every
     replay advances the factors exactly like an eager clock."""
     import torch
 
@@ -652,8 +675,9 @@ def test_seq_clock_inside_a_callers_graph_capture(gpu):
     side = torch.cuda.Stream()
     res = []
     for captured in (False, True):
-        with gpu.PsMf(N, M, K, 4, 0, 0.02, 0.05, step=gpu.STEP_SEQ, strata=5, stream=side) as g:
+        with gpu.PsMf(N, M, K, 4, 0, 0.02, 0.05, step=gpu.STEP_SEQ, strata=5, stream=side, seq_lists=lists) as g:
             g.load_ratings(user, item, val)
+            assert (g.export_index(gpu.IDX_SEQ_LISTS).size > 0) == bool(lists)
             g.set_factors(L0, R0)
             torch.cuda.synchronize()
             if captured:

@@ -1,10 +1,10 @@
 """The sequential step by lists (one launch per clock) and by chains (MI355X) against the oracle.
 
-The layout takes lists where they are estimated faster; the first cases are on that side: lists
-shorter and longer than a block of 60 records, a user with every item, an item with every user
-(its row is handed from list to list), ranks on both sides of each lane width, a row version per
-client, and more workers than users.  The last case is on the chains' side (few long chains,
-one worker), replayed from graphs and launched one by one.
+Every case runs in both forms, which must agree bit for bit: lists shorter and longer than a block of
+60 records, a user with every item, an item with every user (its row is handed from list to list),
+ranks on both sides of each lane width, a row version per client, more workers than users, one
+sub-epoch and more than items.  The last case is one worker's long chains, replayed from graphs and
+launched one by one.
 """
 import numpy as np
 import pytest
@@ -28,23 +28,28 @@ def problem(seed, N, M, nnz, K, hot_user=False, hot_item=False):
     return user, item, val, rng.normal(0, 0.1, (N, K)).astype(np.float32), rng.normal(0, 0.1, (M, K)).astype(np.float32)
 
 
-def both(w, N, M, K, P, s, B, G, policy, clocks, graphs=None):
+def by_hand(w, N, M, K, P, s, B, G, policy, clocks, lists, graphs=None):
     from paper_1410_8043_amd import ps_mf
 
     user, item, val, L0, R0 = w
     with ps_mf.PsMf(N, M, K, P, s, 0.01, 0.05, policy=policy, step=ps_mf.STEP_SEQ, B=B, mb_seed=9, strata=G,
-                    seq_graphs=graphs) as g:
+                    seq_graphs=graphs, seq_lists=lists) as g:
         g.load_ratings(user, item, val)
+        assert all(g.export_index(ps_mf.IDX_SEQ_LISTS, b).size == (16 * P + 1 if lists else 0) for b in range(B))
         g.set_factors(L0, R0)
         g.clock(clocks)
-        L, R = g.get_factors()
+        return g.get_factors()
+
+
+def by_oracle(w, N, M, K, P, s, B, G, policy, clocks):
+    user, item, val, L0, R0 = w
     o = oracle.Oracle(N, M, K, P, s, 0.01, 0.05, policy, oracle.SEQ, B, 9, strata=G)
     o.load(user, item, val)
     o.set_factors(L0, R0)
     o.clock(clocks)
     Lo, Ro = o.get_factors()
     o.close()
-    return L, R, Lo, Ro
+    return Lo, Ro
 
 
 @pytest.mark.parametrize("N, M, nnz, K, P, s, B, G, policy, hot_user, hot_item", [
@@ -57,17 +62,23 @@ def both(w, N, M, K, P, s, B, G, policy, clocks, graphs=None):
     (20, 400, 1500, 128, 37, 3, 1, 256, oracle.ESSP_ROW, True, False),
     (1000, 40, 6000, 16, 4, 2, 1, 1, oracle.SSP_LAZY, False, True),
 ])
-def test_lists_match_the_oracle(N, M, nnz, K, P, s, B, G, policy, hot_user, hot_item):
+def test_lists_and_chains_match_the_oracle(N, M, nnz, K, P, s, B, G, policy, hot_user, hot_item):
     print(f"lists: N={N} M={M} nnz={nnz} K={K} P={P} s={s} B={B} G={G} policy={policy}", flush=True)
-    L, R, Lo, Ro = both(problem(nnz, N, M, nnz, K, hot_user, hot_item), N, M, K, P, s, B, G, policy, 2 * B + s)
+    w = problem(nnz, N, M, nnz, K, hot_user, hot_item)
+    args = (w, N, M, K, P, s, B, G, policy, 2 * B + s)
+    L, R = by_hand(*args, lists=1)
+    Lc, Rc = by_hand(*args, lists=0)
+    Lo, Ro = by_oracle(*args)
     assert np.isfinite(Lo).all() and max(np.abs(L - Lo).max(), np.abs(R - Ro).max()) <= TOL
+    assert np.array_equal(L, Lc) and np.array_equal(R, Rc)
 
 
 def test_long_chains_match_the_oracle_with_and_without_graphs():
     N, M, nnz, K, P, G = 4000, 40, 60_000, 20, 1, 8
     print(f"chains: N={N} M={M} nnz={nnz} K={K} P={P} G={G}", flush=True)
-    w = problem(1, N, M, nnz, K)
-    L, R, Lo, Ro = both(w, N, M, K, P, 1, 1, G, oracle.SSP_LAZY, 5, graphs=True)
+    args = (problem(1, N, M, nnz, K), N, M, K, P, 1, 1, G, oracle.SSP_LAZY, 5)
+    L, R = by_hand(*args, lists=0, graphs=True)
+    Lo, Ro = by_oracle(*args)
     assert np.isfinite(Lo).all() and max(np.abs(L - Lo).max(), np.abs(R - Ro).max()) <= TOL
-    Le, Re, _, _ = both(w, N, M, K, P, 1, 1, G, oracle.SSP_LAZY, 5, graphs=False)
+    Le, Re = by_hand(*args, lists=0, graphs=False)
     assert np.array_equal(L, Le) and np.array_equal(R, Re)
