@@ -936,6 +936,43 @@ void build_seq(const LayoutParams &p, BlockLayout &L, const std::vector<int32_t>
 
 }  // namespace
 
+// A lane group sweeps its unit 8 ratings at a time, about 1.2 us each, so one unit of 256 takes 38 us: the
+// whole of a small block's sweep, whose other units are done long before.  Shorter units cost the
+// popular rows more partial rows.  Measured, ms per clock with 256 / 128 / 64 / 32 ratings (K): 100K (128)
+// .069 / .051 / .041 / .042; 225K (64, a version per row) .073 / .056 / .047 / .044; 412K (100) .097 / .061 /
+// .052 / .055; 1.0M (256) .149 / .137 / .134 / .149; 1.2M (64) .111 / .096 / .091 / .090; 2.0M (256) .297 /
+// .286 / .295 / .326; 4.0M (32) .087 / .078 / .077 / .082; 4.0M (128) .227 / .218 / .225 / .246; 6.0M (200)
+// .632 / .645 / .691; 8.0M (64) .231 / .230 / .240; wide rows: 200K (256) .078 / .079 / .080 / .088; 1.4M
+// (256) .153 / .149 / .158 / .180; 1.4M (512) .323 / .278 / .306 / .323.  Three kinds of blocks want longer ones:
+// * a user's partial rows are summed one after the other, 0.14 us each, an item's in 1024 / Kp lanes;
+//   0.15 us a rating of length against that is least at about the root of the ratings of the
+//   busiest row.  Sweep and commit, us, with 256 / 128 / 64 / 32: 10 users of 20,000 (K = 64) 57 / 53 / 66 /
+//   107; one of 100,000 94 / 123 / 205 / 378; 30,000 x 6000 with users of up to 6000 57 / 45 / 44 / 50; 10
+//   items of 80,000 (K = 256) 197 / 200 / 214 / 244;
+// * users of 256 ratings and more on average whose units gather from an item table beyond an XCD's L2
+//   find rows there that the other users of the moment read, as long as all of them walk the items
+//   in step: 1M ratings of 2000 users over 20,000 items, K = 128 81 / 75 / 89 / 95, K = 256 138 / 163 / 186 /
+//   199; 500 over 60,000, K = 128 109 / 112 / 128 / 130; 2M 157 / 191 / 195 / 199.  Within the L2 (5000 x
+//   5000, K = 128) 120 / 105 / 102 / 114; in a block too small to fill the chip (200K of 500 over 60,000, K =
+//   128) 91 / 74 / 74 / 77.
+int32_t unit_length(const LayoutParams &p, const BlockLayout &L) {
+  if (p.unit_max > 0) return p.unit_max;
+  const int64_t n = L.nnz, floats = n * p.row_floats;
+  int32_t len = n < (int64_t{1} << 18) && floats < (int64_t{1} << 25)   ? 32
+                : n < 1'500'000 && floats < (int64_t{1} << 28) ? 64
+                : n < 6'000'000                                ? 128
+                                                               : 256;
+  int64_t rated = 0, most = 0;
+  for (int32_t c : L.ucount) {
+    rated += c > 0;
+    most = std::max<int64_t>(most, c);
+  }
+  if (n >= 256 * rated && p.items * p.row_floats * 4 > (int64_t{4} << 20) && floats >= (int64_t{1} << 25)) len = 256;
+  for (int32_t c : L.icount) most = std::max<int64_t>(most, static_cast<int64_t>(c) * p.row_floats / 1024);
+  while (len < 256 && 4 * static_cast<int64_t>(len) * len <= most) len *= 2;
+  return len;
+}
+
 int build_layout(const LayoutParams &p, const int32_t *user, const int32_t *item, const float *val, int64_t n,
                  std::vector<BlockLayout> &out, std::string &err) {
   try {
@@ -1095,6 +1132,7 @@ int build_layout(const LayoutParams &p, const int32_t *user, const int32_t *item
       for (int64_t x = 0; x < nb; ++x) in_units[x] = !in_dense[x] && !heavy[ent_user[x]] && hot_pos[L.col[x]] < 0;
       // ---- units.  Tiles start at the L2-sized row count and grow (x2) while the units
       // would average fewer than 16 ratings (each unit costs one partial row).
+      const int32_t unit_len = unit_length(p, L);
       const int64_t min_avg = 16;
       int64_t n_units_entries = 0;
       for (int64_t x = 0; x < nb; ++x) n_units_entries += in_units[x];
@@ -1127,7 +1165,7 @@ int build_layout(const LayoutParams &p, const int32_t *user, const int32_t *item
           return static_cast<int32_t>(ucls[ent_user[e]] * nt + L.col[e] / rows);
         };
         const std::function<int32_t(int64_t)> ct = [nt](int64_t t) { return static_cast<int32_t>(t / nt); };
-        build_units(nb, N, nt * p.nclass, xr, yr, tl, ct, L.val, p.unit_max, in_units, extra_u, base_u, L.by_user);
+        build_units(nb, N, nt * p.nclass, xr, yr, tl, ct, L.val, unit_len, in_units, extra_u, base_u, L.by_user);
         assign_cell_rows(L.cells_user, L.dense_user, base_u);
         L.partial_rows_user = L.by_user.x_pp[N];
       }
@@ -1178,7 +1216,7 @@ int build_layout(const LayoutParams &p, const int32_t *user, const int32_t *item
         for (int32_t c = 0; c < p.nclass; ++c)
           for (int64_t t = cls_base[c]; t < cls_base[c + 1]; ++t) tile_cls[t] = c;
         const std::function<int32_t(int64_t)> ct = [&](int64_t t) { return tile_cls[t]; };
-        build_units(nb, M, nt, xr, yr, tl, ct, L.val, p.unit_max, in_units, extra_i, base_i, L.by_item);
+        build_units(nb, M, nt, xr, yr, tl, ct, L.val, unit_len, in_units, extra_i, base_i, L.by_item);
         assign_cell_rows(L.cells_item, L.dense_item, base_i);
         L.partial_rows_item = L.by_item.x_pp[M];
       }

@@ -181,7 +181,8 @@ struct LayoutParams {
   int32_t threads = 1;
   int64_t tile_rows_item = 1 << 30; // items per tile of the user-major sweep
   int64_t tile_rows_user = 1 << 30; // users per tile of the item-major sweep
-  int32_t unit_max = 1024;          // ratings per work unit
+  int32_t unit_max = 1024;          // ratings per work unit (0: from each block's ratings, see unit_length)
+  int32_t row_floats = 64;          // floats of a factor row in memory (Kp)
   int32_t cell_rows = 0;            // ts: gathered rows per LDS sub-tile (0: no cells)
   int32_t cell_groups = 0;          // ng: lane groups per cell workgroup
   int64_t heavy_min = 1 << 30;      // users with at least this many ratings in the block go to cells
@@ -200,6 +201,9 @@ struct LayoutParams {
   int32_t seq_groups = 0;           // G > 0: build the sequential step's order (SeqSet) instead of
                                     // units, cells and dense tiles
 };
+
+// Ratings per work unit of a block: unit_max, or by the block's size, rank and busiest rows (32 to 256).
+int32_t unit_length(const LayoutParams &p, const BlockLayout &L);
 
 // Validates the COO input (EINVAL message in err) and fills one BlockLayout per block.
 // Returns 0, -1 (invalid input) or -2 (allocation failure).

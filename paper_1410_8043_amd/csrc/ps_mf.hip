@@ -2838,18 +2838,6 @@ int ps_mf_load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, con
 }  // extern "C"
 
 namespace {
-// Ratings per work unit, from the ratings of a block.  A lane group sweeps its unit 8 ratings at
-// a time, about 1.2 us each, so one unit of 256 takes 38 us: the whole of a small block's sweep,
-// whose other units are done long before.  Shorter units cost the popular rows more partial
-// rows.  Measured, ms per clock with 256 / 128 / 64 / 32 ratings (K): 100K (128) .069 / .051 /
-// .041 / .042; 225K (64, a version per row) .073 / .056 / .047 / .044; 412K (100) .097 / .061 /
-// .052 / .055; 1.0M (256) .149 / .137 / .134 / .149; 1.2M (64) .111 / .096 / .091 / .090; 2.0M
-// (256) .297 / .286 / .295 / .326; 4.0M (32) .087 / .078 / .077 / .082; 4.0M (128) .227 / .218 /
-// .225 / .246; 6.0M (200) .632 / .645 / .691; 8.0M (64) .231 / .230 / .240.
-int32_t auto_unit_max(int64_t block_ratings) {
-  return block_ratings < (int64_t{1} << 18) ? 32 : block_ratings < 1'500'000 ? 64 : block_ratings < 6'000'000 ? 128 : 256;
-}
-
 int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const float *value, int64_t n) {
   if (h->loaded) return fail(h, PS_MF_ESTATE, "ratings are already loaded");
   if (n < 0 || (n > 0 && (!user || !item || !value))) return fail(h, PS_MF_EINVAL, "bad rating arrays");
@@ -2884,7 +2872,8 @@ int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const flo
                           ? std::max<int64_t>(64, h->item_tile_bytes / (static_cast<int64_t>(h->Kp) * 4))
                           : 4 * lp.tile_rows_user;
   // with the cells switched off by hand the split is the caller's, and units are as long as documented
-  lp.unit_max = h->unit_max > 0 ? h->unit_max : h->cells ? auto_unit_max(n / h->B) : 256;
+  lp.unit_max = h->unit_max > 0 ? h->unit_max : h->cells ? 0 : 256;
+  lp.row_floats = h->Kp;
   // The automatic split sends ratings to dense tiles and LDS cells only when the minibatch
   // blocks are large: both pay fixed costs (a partial row per cell row, workgroups that
   // each sweep a few steps) that a small block does not amortize.  Measured on the

@@ -514,3 +514,32 @@ def test_automatic_unit_length_follows_the_blocks(nnz, B, longest):
             g.load_ratings(u, i, v)
             units.append([int(x) for x in g.export_index(m.IDX_SPLIT)])
     assert units[0] == units[1] and units[2] == units[3] and units[0] != units[2], units
+
+
+@pytest.mark.parametrize("N, M, nnz, K, longest", [
+    (10, 20_000, 199_990, 8, 128),      # few users of 20,000 ratings: their partial rows are summed one by one
+    (1, 100_000, 99_999, 64, 256),      # one user
+    (100, 20_000, 200_000, 8, 32),      # users of 2000 ratings are not busy enough for that
+    (80_000, 10, 799_990, 256, 128),    # items of 80,000 ratings at a wide rank, four rows at a time
+    (80_000, 10, 799_990, 16, 64),      # at a narrow one 64 rows are summed at a time
+    (2000, 2000, 200_000, 256, 64),     # as many floats as 800,000 ratings at K = 64
+    (20_000, 500, 1_100_000, 256, 128),
+    (500, 60_000, 300_000, 128, 256),   # busy users over an item table beyond an XCD's L2
+    (500, 4000, 300_000, 128, 64),      # the table fits
+    (2000, 60_000, 300_000, 128, 64),   # users of 150 ratings
+])
+def test_automatic_unit_length_follows_rank_and_busy_rows(N, M, nnz, K, longest):
+    """Where a row of the block has very many ratings, where rows are wide and where the users'
+    units gather from a large table, the automatic length is that of the rule, which the
+    counts of the partial rows show (those of half and of twice the length differ)."""
+    from paper_1410_8043_amd import ps_mf as m
+
+    u, i = (np.arange(nnz) % N).astype(np.int32), (np.arange(nnz) // N % M).astype(np.int32)
+    if N > M:
+        u, i = (np.arange(nnz) // M % N).astype(np.int32), (np.arange(nnz) % M).astype(np.int32)
+    units = []
+    for length in (None, longest, longest // 2, longest * 2):
+        with m.PsMf(N, M, K, 1, 0, 0.01, 0.05, host_only=True, unit_max=length) as g:
+            g.load_ratings(u, i, np.ones(nnz, np.float32))
+            units.append([int(x) for x in g.export_index(m.IDX_SPLIT)])
+    assert units[0] == units[1] and units[0] != units[2] and units[0] != units[3], units
