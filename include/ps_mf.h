@@ -82,8 +82,7 @@ typedef struct ps_mf ps_mf_t;
                                   >= 1 */
 #define PS_MF_OPT_UNIT_MAX 8   /* ratings per sweep work unit; >= 1 (default: automatic for each
                                   block, from 32 where it has few ratings to 256 from 6 million
-                                  on, longer where a row has very many; 256
-                                  with PS_MF_OPT_CELLS 0) */
+                                  on, longer where a row has very many) */
 #define PS_MF_OPT_CELLS 9      /* 1 (default): sweep the dense part (users with many ratings) through
                                   LDS-staged cells; 0: every rating through the L2 work units */
 #define PS_MF_OPT_HEAVY_MIN 10 /* ratings in a block from which a user's ratings go to the cells;

@@ -2871,8 +2871,7 @@ int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const flo
   lp.tile_rows_item = h->item_tile_bytes > 0
                           ? std::max<int64_t>(64, h->item_tile_bytes / (static_cast<int64_t>(h->Kp) * 4))
                           : 4 * lp.tile_rows_user;
-  // with the cells switched off by hand the split is the caller's, and units are as long as documented
-  lp.unit_max = h->unit_max > 0 ? h->unit_max : h->cells ? 0 : 256;
+  lp.unit_max = h->unit_max;
   lp.row_floats = h->Kp;
   // The automatic split sends ratings to dense tiles and LDS cells only when the minibatch
   // blocks are large: both pay fixed costs (a partial row per cell row, workgroups that

@@ -468,7 +468,8 @@ def test_user_major_item_tiles_split_the_units(item_tile_bytes):
     v = rng.integers(1, 6, cells.size).astype(np.float32)
     out = []
     for itb in (None, item_tile_bytes):
-        with m.PsMf(N, M, K, 8, 3, 0.01, 0.05, host_only=True, item_tile_bytes=itb, dense_min=0, cells=0) as g:
+        with m.PsMf(N, M, K, 8, 3, 0.01, 0.05, host_only=True, item_tile_bytes=itb, dense_min=0, cells=0,
+                    unit_max=256) as g:
             g.load_ratings(u, i, v)
             out.append(g.export_index(m.IDX_SPLIT))
     assert out[0][2] == out[1][2] == cells.size
@@ -499,8 +500,8 @@ def test_automatic_split_uses_dense_tiles_and_cells_only_on_large_blocks():
 @pytest.mark.parametrize("nnz, B, longest", [(200_000, 1, 32), (600_000, 1, 64), (600_000, 4, 32)])
 def test_automatic_unit_length_follows_the_blocks(nnz, B, longest):
     """Without options, units are cut at 32 ratings in blocks below 2^18 ratings, at 64 below 1.5
-    million; with the cells switched off by hand they keep the documented 256.  Users of
-    250 ratings are cut differently by each, which the exported counts show."""
+    million, with the cells and without.  Users of 250 ratings are cut differently by each,
+    which the exported counts show."""
     from paper_1410_8043_amd import ps_mf as m
 
     N, M = nnz // 250, 1000
@@ -513,7 +514,7 @@ def test_automatic_unit_length_follows_the_blocks(nnz, B, longest):
         with m.PsMf(N, M, 16, 4, 1, 0.01, 0.05, B=B, mb_seed=3, host_only=True, **more) as g:
             g.load_ratings(u, i, v)
             units.append([int(x) for x in g.export_index(m.IDX_SPLIT)])
-    assert units[0] == units[1] and units[2] == units[3] and units[0] != units[2], units
+    assert units[0] == units[1] == units[2] and units[0] != units[3], units
 
 
 @pytest.mark.parametrize("N, M, nnz, K, longest", [
