@@ -619,7 +619,8 @@ __global__ __launch_bounds__(kWave) void k_lda_sweep(SweepArgs a) {
 //   LPR lanes per row, VW counts per lane and load, so 64 / LPR rows per load and kCommitRows of
 //   those in flight (a popular word has a writer in nearly every worker).
 // Bound by reading the writers' rows and the tags, in pieces of 400 bytes from a 20 GB table at 9.7M
-// tokens, V = 100,000, K = 100, P = 512: 0.64 ms, 0.96 with one wavefront per word.
+// tokens, V = 100,000, K = 100, P = 512: 0.41 ms, 0.96 with one wavefront per word (0.64 with each row's
+// list entry read from LDS right before its load: at V = 300, P = 700, K = 50 133 us, now 45).
 // Workgroup 0 adds the workers' topic-total changes to the last row.
 constexpr int kCommitThreads = 256, kCommitWords = 16, kCommitWorkers = 512, kCommitRows = 8;
 struct CommitArgs {
@@ -699,11 +700,15 @@ __global__ __launch_bounds__(kCommitThreads) void k_lda_commit(CommitArgs a) {
 #pragma unroll
       for (int c = 0; c < CH; ++c) acc[c] = 0;
       for (int x0 = sub; x0 < n; x0 += kCommitRows * subs) {
+        // all list entries before the first row: read one by one, each row's load waited for its own
+        int at[kCommitRows];
+#pragma unroll
+        for (int u = 0; u < kCommitRows; ++u) at[u] = who[min(x0 + u * subs, n - 1)];
         Vec t[kCommitRows][CH];
 #pragma unroll
         for (int u = 0; u < kCommitRows; ++u) {
           const int x = x0 + u * subs;
-          const int32_t *r = a.delta + static_cast<int64_t>(p0 + who[x < n ? x : x0]) * a.V * a.K + row;
+          const int32_t *r = a.delta + static_cast<int64_t>(p0 + at[u]) * a.V * a.K + row;
 #pragma unroll
           for (int c = 0; c < CH; ++c) {
             const int v = l + c * a.lpr;
@@ -899,9 +904,8 @@ void launch_sweep(const SweepArgs &a, int P, bool flat, hipStream_t st) {
 }
 
 // Words per workgroup: 16 where that still makes a thousand workgroups, fewer for small
-// vocabularies, down to one per wavefront.  4 / 8 / 16 / 32 words (32: a CU holds half as many
-// workgroups) measured 676 / 667 / 635 / 733 us at V = 100,000, P = 512 and 80 / 80 / 80 / 122 us at
-// V = 20,000, P = 64 (K = 100).
+// vocabularies, down to one per wavefront.  4 / 8 / 16 / 32 words measured 468 / 414 / 413 / 411 us at
+// V = 100,000, P = 512 and 58 / 59 / 60 / 62 us at V = 20,000, P = 64 (K = 100).
 int commit_words(int64_t V) { return V >= 16'384 ? kCommitWords : V >= 8192 ? 8 : 4; }
 
 template <int VW, int CH>
