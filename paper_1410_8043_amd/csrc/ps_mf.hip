@@ -1015,7 +1015,7 @@ struct CommitArgs {
   const int32_t *cls_slot;    // [nclass]
   const float *partial;       // item-major partial rows
   const int64_t *item_pp;     // [items + 1]
-  const int32_t *many;        // the items of more than few_rows(Kp) partial rows
+  const int32_t *many;        // the items of more than few_rows(Kp) partial rows (k_commit<true>)
   float eta, lambda;
   int32_t rowmean;
   const int32_t *rs_i;        // per-row policies: [nclass * items] ring slot of each class's view of an item row
@@ -1055,41 +1055,46 @@ __device__ __forceinline__ float4 item_row(const CommitArgs &a, int n, float4 rc
                      rc.z + sc * (d.z - a.lambda * lam.z), rc.w + sc * (d.w - a.lambda * lam.w));
 }
 
-// The items of at most few_rows(Kp) partial rows, one thread
-// per 4 columns: nothing but the row's own loads, in two levels.  A workgroup per item left most
-// of its threads without a row and waited for LDS and the classes' views after the partial rows.
-// At Kp = 256 and 512 a workgroup has 4 and 2 rows in flight of an item's and leaves few threads idle:
-// there only the items without a partial row are taken.  The sums are those of commit_item to the
-// bit (it has 8 row lanes or more up to Kp = 128, so each adds one row).
+// The items of at most few_rows(Kp) partial rows (k_commit<true>), one thread per 4 columns: nothing
+// but the row's own loads, in two levels.  A workgroup per item left most of its threads without a
+// row and waited for LDS and the classes' views after the partial rows.  At Kp = 256 and 512 a
+// workgroup has 4 and 2 of an item's rows in flight and leaves few threads idle: there only the items
+// without a partial row are taken.  The sums are those of commit_item to the bit (it has 8 row lanes
+// or more up to Kp = 128, so each adds one row).
 // k_commit, a workgroup for each item / this, us a clock: 70,000 + 14,000 rows at K = 64, 1.2M ratings
-// 28.7 / 17.9; 30,000 + 6000 at K = 64 with a version per row 14.5 / 11.2; 12,345 + 6789 at Kp = 128 12.9 /
-// 10.1; 1000 + 500 at K = 16 5.9 / 4.0; 60,007 + 10,007 at K = 128, nearly all items of many
-// rows, 49.7 / 51.2.  At Kp = 256 with 8 here too: 40.9 / 45.6.  (The users' workgroups last: 21.4, 12.2, 11.4.)
+// 28.7 / 17.9; 30,000 + 6000 at K = 64 with a version per row 14.5 / 11.1; 12,345 + 6789 at Kp = 128 12.9 /
+// 10.0; 1000 + 500 at K = 16 5.9 / 3.9.  At Kp = 256 with 8 here too: 40.9 / 45.6.  (The users'
+// workgroups last: 21.4, 12.2, 11.4.)  Where most items have more rows, every item takes a workgroup
+// and the kernel has no such path (k_commit<false>): with it, for all rows of the table, 60,007 +
+// 10,007 at K = 128 took 52.2 instead of 48.9, 200,000 + 100,000 at K = 256 with 200,000 ratings 235 instead
+// of 191.
 __host__ __device__ constexpr int few_rows(int Kp) { return Kp <= 128 ? 8 : 0; }
-__device__ __forceinline__ void commit_item_few(const CommitArgs &a, int64_t idx) {
+__device__ __forceinline__ void commit_item_few(const CommitArgs &a, int64_t at) {
   const int q4 = a.Kp / 4;  // a power of two
-  const int64_t j = idx >> __builtin_ctz(q4);
-  if (j >= a.items) return;
+  if (at >= a.items * q4) return;
+  // a table has fewer than 2^28 float4s
+  const uint32_t idx = static_cast<uint32_t>(at), j = idx >> __builtin_ctz(q4), k4 = idx & (q4 - 1);
   float4 *R4 = reinterpret_cast<float4 *>(a.ring + a.r_off);
   const int64_t ss4 = a.slot_stride / 4;
   const int n = a.icount[j];
-  const int64_t p0 = a.item_pp[j], p1 = a.item_pp[j + 1];
-  if (p1 - p0 > few_rows(a.Kp)) return;  // in the list of the others
+  const int64_t p0 = a.item_pp[j];
+  const int rows = static_cast<int>(a.item_pp[j + 1] - p0);
+  if (rows > few_rows(a.Kp)) return;  // in the list of the others
   const float4 rc = R4[a.slot_c * ss4 + idx];
   if (n == 0) {
     if (a.slot_n != a.slot_c) R4[a.slot_n * ss4 + idx] = rc;
     return;
   }
   ClassRows v = load_classes(a, R4, j, idx, 0);
-  const f32x4 *part4 = reinterpret_cast<const f32x4 *>(a.partial) + (idx - j * q4);
+  const f32x4 *part4 = reinterpret_cast<const f32x4 *>(a.partial) + p0 * q4 + k4;
   float4 d = make_float4(0.f, 0.f, 0.f, 0.f), lam = d;
-  for (int64_t p = p0; p < p1; p += 4) {
+  for (int p = 0; p < rows; p += 4) {
     f32x4 t[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) t[u] = ld_partial(part4 + min(p + u, p1 - 1) * q4);
+    for (int u = 0; u < 4; ++u) t[u] = ld_partial(part4 + min(p + u, rows - 1) * q4);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      if (p + u < p1) { d.x += t[u][0]; d.y += t[u][1]; d.z += t[u][2]; d.w += t[u][3]; }
+      if (p + u < rows) { d.x += t[u][0]; d.y += t[u][1]; d.z += t[u][2]; d.w += t[u][3]; }
     }
   }
   add_classes(lam, v);
@@ -1101,9 +1106,9 @@ __device__ __forceinline__ void commit_item_few(const CommitArgs &a, int64_t idx
 }
 
 // R^{c+1}_j = R^c_j + scale_j (sum of j's partial rows - lambda sum_class n_j^(class) R^{v(class)}_j).
-// One workgroup per item of more than few_rows(Kp) partial rows: thread t sums the float4 column t mod (Kp/4) of every
-// (kBlock / (Kp/4))-th partial row, starting at row t / (Kp/4); the column sums are then
-// added in row-lane order through LDS (popular items own thousands of partial rows).
+// One workgroup per item (k_commit<true>: of more than few_rows(Kp) partial rows): thread t sums the
+// float4 column t mod (Kp/4) of every (kBlock / (Kp/4))-th partial row, starting at row
+// t / (Kp/4); the column sums are then added in row-lane order through LDS (popular items own thousands of partial rows).
 __device__ __forceinline__ void commit_item(const CommitArgs &a, int64_t j, float4 *red) {
   const int q4 = a.Kp / 4;
   const int lanes = kBlock / q4;  // row lanes: Kp is a power of two in [8, 512], so 2..128
@@ -1112,18 +1117,21 @@ __device__ __forceinline__ void commit_item(const CommitArgs &a, int64_t j, floa
   const int64_t ss4 = a.slot_stride / 4;
   const int64_t idx = j * q4 + k4;
   const int n = a.icount[j];
-  const int64_t p0 = a.item_pp[j], p1 = a.item_pp[j + 1];
-  float4 rc = make_float4(0.f, 0.f, 0.f, 0.f);
+  const int64_t p0 = a.item_pp[j];
+  const int rows = static_cast<int>(a.item_pp[j + 1] - p0);
+  float4 rc;  // lane 0's alone; given a value elsewhere, the load would be waited for at once
   if (lane == 0) rc = R4[a.slot_c * ss4 + idx];  // loaded before the partial rows
   if (n == 0) {  // uniform over the workgroup; a dense tile gives partial rows to items without a rating too
     if (lane == 0) R4[a.slot_n * ss4 + idx] = rc;
     return;
   }
   float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
-  const f32x4 *part4 = reinterpret_cast<const f32x4 *>(a.partial);
+  // this lane's rows lie lanes * q4 = kBlock columns apart (their number without a division)
+  const f32x4 *part4 = reinterpret_cast<const f32x4 *>(a.partial) + (p0 + lane) * q4 + k4;
+  const int mine = (rows - lane + lanes - 1) >> __builtin_ctz(lanes);
 #pragma unroll 4
-  for (int64_t p = p0 + lane; p < p1; p += lanes) {
-    const f32x4 t = ld_partial(part4 + p * q4 + k4);
+  for (int p = 0; p < mine; ++p) {
+    const f32x4 t = ld_partial(part4 + static_cast<int64_t>(p) * kBlock);
     d.x += t[0]; d.y += t[1]; d.z += t[2]; d.w += t[3];
   }
   red[threadIdx.x] = d;
@@ -1191,15 +1199,18 @@ __global__ __launch_bounds__(kBlock) void k_row_views(RowViewArgs a) {
     if (hist[t]) atomicAdd(a.stale + t, hist[t]);
 }
 
-// Version c+1 of both factors in one launch: workgroups [0, grid_users) finalize L, the next
-// nmany commit an item of many partial rows each and the rest the other items, one thread
-// per 4 columns of a row for L and those.  They write different rows of the new slot and read
-// only partial rows and versions <= c.
+// Version c+1 of both factors in one launch: workgroups [0, grid_users) finalize L, one thread per 4
+// columns of a row; the others commit an item each (Few: the next nmany an item of many partial
+// rows each and the rest the other items, one thread per 4 columns).  They write different rows
+// of the new slot and read only partial rows and versions <= c.
+template <bool Few>
 __global__ __launch_bounds__(kBlock) void k_commit(FinalArgs fa, CommitArgs ca, int32_t grid_users, int32_t nmany) {
   __shared__ float4 red[kBlock];
   const int32_t b = static_cast<int32_t>(blockIdx.x) - grid_users;
   if (b < 0)
     finalize_users(fa, static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x);
+  else if (!Few)
+    commit_item(ca, b, red);
   else if (b < nmany)
     commit_item(ca, ca.many[b], red);
   else
@@ -1890,7 +1901,9 @@ struct DeviceUnits {
   float *val = nullptr;
   int32_t *unit_x = nullptr, *unit_cls = nullptr, *unit_len = nullptr, *unit_out = nullptr;
   int64_t *unit_beg = nullptr, *xcd_off = nullptr, *x_pp = nullptr;
-  int32_t *x_many = nullptr;  // item-major set: the items of more than few_rows(Kp) partial rows
+  // item-major set: the items of more than few_rows(Kp) partial rows where most have no more (null:
+  // every item takes a workgroup of the commit)
+  int32_t *x_many = nullptr;
   int32_t nmany = 0;
   uint8_t *sole = nullptr;  // user-major set: rows whose only partial row is one unit's
 };
@@ -2538,7 +2551,8 @@ int one_clock(ps_mf_t *h) {
   ca.lambda = h->lambda;
   ca.rowmean = rowmean;
   ca.rs_i = per_row_policy(h) ? h->slot_i : nullptr;
-  const int64_t grid_users = (nfin + kBlock - 1) / kBlock, grid_few = (h->M * h->Kp / 4 + kBlock - 1) / kBlock;
+  const int64_t grid_users = (nfin + kBlock - 1) / kBlock;
+  const int64_t grid_items = ca.many ? db.by_item.nmany + (h->M * h->Kp / 4 + kBlock - 1) / kBlock : h->M;
   hipEvent_t ev = nullptr;
   if ((rc = record(h, &ev))) return rc;
   if (per_row_policy(h) && (rc = row_views(h, db, c))) return rc;
@@ -2655,9 +2669,10 @@ int one_clock(ps_mf_t *h) {
                        fa, ca);
     HIP_TRY(h, hipGetLastError());
   }
-  const int32_t nmany = db.by_item.nmany;
-  hipLaunchKernelGGL(k_commit, dim3(static_cast<unsigned>(grid_users + nmany + grid_few)), dim3(kBlock), 0, h->stream, fa,
-                     ca, static_cast<int32_t>(grid_users), nmany);
+  const dim3 grid(static_cast<unsigned>(grid_users + grid_items));
+  const int32_t gu = static_cast<int32_t>(grid_users), nmany = db.by_item.nmany;
+  if (ca.many) hipLaunchKernelGGL(k_commit<true>, grid, dim3(kBlock), 0, h->stream, fa, ca, gu, nmany);
+  else hipLaunchKernelGGL(k_commit<false>, grid, dim3(kBlock), 0, h->stream, fa, ca, gu, nmany);
   HIP_TRY(h, hipGetLastError());
   if ((rc = record_end(h, PS_MF_KERNEL_COMMIT, ev))) return rc;
 
@@ -2987,8 +3002,10 @@ int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const flo
       std::vector<int32_t> many;
       for (int64_t j = 0; j < h->M; ++j)
         if (L.by_item.x_pp[j + 1] - L.by_item.x_pp[j] > few_rows(h->Kp)) many.push_back(static_cast<int32_t>(j));
-      d.by_item.nmany = static_cast<int32_t>(many.size());
-      if ((r = upload(h, &d.by_item.x_many, many))) return undo(r);
+      if (2 * static_cast<int64_t>(many.size()) < h->M) {  // both sides measured at commit_item_few
+        d.by_item.nmany = static_cast<int32_t>(many.size());
+        if ((r = upload(h, &d.by_item.x_many, many))) return undo(r);
+      }
     }
     // partial rows of units and cells, + the row the padding units write
     max_units_u = std::max<int64_t>(max_units_u, L.partial_rows_user + 1);
