@@ -1,8 +1,9 @@
 """The squared loss at the edges of its segments (MI355X).
 
-A lane group sweeps up to 64 ratings of one user, 8 pairs at a time, read 8 ahead from any
-4-byte address.  Users of 1, 7, 8, 9, 63, 64, 65, 127, 129, 511, 512 and 513 ratings follow one
-another here, so segments start at every remainder of 8, and the last one ends the arrays.
+A lane group sweeps up to 64 ratings of one user (from rank 129 on, up to 95 where they are all, else 48
+to 80), 8 pairs at a time, read 8 ahead from any 4-byte address.  Users of 1, 7, 8, 9, 63, 64, 65, 95,
+96, 127, 129, 159, 160, 511, 512 and 513 ratings follow one another here, so segments start at
+every remainder of 8, and the last one ends the arrays.
 The sum must be that of the same residuals in 64 bits: a residual holds K products summed in
 32 bits, whose relative error is at most (K + 1) 2^-24 of the products' magnitudes, at most
 2^-24 * 513 * 2 of the squares' sum at these values; 1e-5 allows a sixth of that.
@@ -12,7 +13,7 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-DEGREES = [1, 7, 8, 9, 63, 64, 65, 127, 129, 511, 512, 513]
+DEGREES = [1, 7, 8, 9, 63, 64, 65, 95, 96, 127, 129, 159, 160, 511, 512, 513]
 
 
 @pytest.mark.parametrize("K", [1, 8, 16, 33, 64, 100, 128, 256, 512])
