@@ -746,21 +746,32 @@ void build_seq_lists(const LayoutParams &p, BlockLayout &L, const std::vector<st
   const int64_t P = p.workers, M = p.items, D = p.seq_list_ahead;
   if (L.nnz == 0 || p.seq_lists == 0) return;
   // Lists or chains, by what each was measured to take (us, MI355X):
-  //   chains: a launch per sub-epoch, 4.5 and 0.33 per rating of its longest chain;
-  //   lists: the most of 0.045 per rating of the busiest worker (its CU's 16 wavefronts), 0.4 per
-  //   rating of the busiest user (one after the other) and 2 per rating of a worker's most rated
-  //   item (handed from list to list).
+  //   chains: a launch per sub-epoch, 4.5 and 0.27 per rating of its longest chain; or, where they
+  //   fill the chip, 3.5 per launch and, on each of 256 CUs, 0.023 per rating and 0.06 per chain;
+  //   lists: the most of 0.045 per rating of the busiest worker (its CU's 16 wavefronts), 0.3 per
+  //   rating of the busiest user (one after the other), 2 per rating of a worker's most rated
+  //   item (handed from list to list) and, on each of 256 CUs, 0.036 per rating; and 0.0012 per
+  //   worker (two workgroups of 16 wavefronts fit a CU, so 512 workers make a round).
+  // What fills the chip takes longer with rows beyond about 110 floats.
   // Measured lists / chains, ms per clock of the block: 20K ratings, P = 4: 0.20 / 1.22; 225K, K =
   // 64, P = 32: 0.50 / 1.41; 2.4M, K = 128, P = 64: 1.57 / 2.60, P = 16: 8.5 / 2.98; 4M, K = 32, P =
   // 256: 0.74 / 2.88; 2M, K = 256, P = 128: 2.70 / 4.53; 9M, K = 128, P = 64: 7.5 / 6.4; 200K, P = 1:
-  // 18 / 2.6.
-  double t_chains = 0;
+  // 18 / 2.6.  With many workers, at 1 / 16 / 256 sub-epochs, us: 200K ratings, K = 16, P = 1024: 44 / 77,
+  // 40 / 109, 43 / 969; P = 4096: 43 / 45, 43 / 109, 45 / 972; P = 16,384: 48 / 37, 47 / 121, 48 / 945; P =
+  // 65,536: 128 / 48, 128 / 126, 130 / 735; 1M ratings, P = 1024: 217 / 314, 127 / 250, 178 / 1119; P =
+  // 4096: 142 / 122, 127 / 261, 140 / 1121; P = 16,384: 144 / 98, 143 / 259, 145 / 1122; P = 65,536: 179 /
+  // 106, 179 / 331, 178 / 924; 4M, K = 32, P = 16,384: 524 / 363, -, 521 / 2483; 1M, K = 512, P = 1024: -,
+  // 773 / 1093, 804 / 2597.  Without the terms for a full chip, lists were taken at 1 sub-epoch too.
+  double t_chains = 0, launches = 0;
   for (int64_t t = 0; t < S.G; ++t) {
     int64_t most = 0;
     for (int64_t ch = S.epoch_chain[t]; ch < S.epoch_chain[t + 1]; ++ch)
       most = std::max(most, S.chain_beg[ch + 1] - S.chain_beg[ch]);
-    t_chains += most > 0 ? 4.5 + 0.33 * static_cast<double>(most) : 0.0;
+    t_chains += most > 0 ? 4.5 + 0.27 * static_cast<double>(most) : 0.0;
+    launches += most > 0;
   }
+  const double wide = std::max(1.0, p.row_floats / 110.0) / 256, nnz = static_cast<double>(L.nnz);
+  t_chains = std::max(t_chains, 3.5 * launches + wide * (0.023 * nnz + 0.06 * static_cast<double>(S.chain_worker.size())));
   int64_t worker_most = 0, item_most = 0;
   const int64_t user_most = *std::max_element(L.ucount.begin(), L.ucount.end());
   {
@@ -782,8 +793,9 @@ void build_seq_lists(const LayoutParams &p, BlockLayout &L, const std::vector<st
       worker_most = std::max(worker_most, work);
     }
   }
-  const double t_lists = std::max({0.045 * static_cast<double>(worker_most), 0.4 * static_cast<double>(user_most),
-                                   2.0 * static_cast<double>(item_most)});
+  const double t_lists = std::max({0.045 * static_cast<double>(worker_most), 0.3 * static_cast<double>(user_most),
+                                   2.0 * static_cast<double>(item_most), wide * 0.036 * nnz}) +
+                         0.0012 * static_cast<double>(P);
   if (worker_most > kSeqListMost || (p.seq_lists < 0 && t_lists >= t_chains)) return;
   // each worker's users to its lists: the busiest user first, to the shortest list so far
   std::vector<std::vector<int32_t>> users_of(static_cast<size_t>(P));

@@ -544,3 +544,16 @@ def test_automatic_unit_length_follows_rank_and_busy_rows(N, M, nnz, K, longest)
             g.load_ratings(u, i, np.ones(nnz, np.float32))
             units.append([int(x) for x in g.export_index(m.IDX_SPLIT)])
     assert units[0] == units[1] and units[0] != units[2] and units[0] != units[3], units
+
+
+@pytest.mark.parametrize("P, G, lists", [(1024, 1, True), (1024, 256, True), (16_384, 1, False), (16_384, 16, True),
+                                         (65_536, 1, False), (65_536, 256, True)])
+def test_sequential_form_counts_the_workgroups(P, G, lists):
+    """200,000 ratings of as many or fewer workers: lists (a workgroup of 16 wavefronts per worker)
+    are taken against 16 and 256 launches, but not by thousands of workers against a single one,
+    where they were measured slower (48 us against 37 at P = 16,384, 128 against 48 at 65,536)."""
+    rng = np.random.default_rng(P + G)
+    N, M, n = max(P, 5000), 500, 200_000
+    with ps_mf.PsMf(N, M, 16, P, 1, 1e-6, 0.05, step=ps_mf.STEP_SEQ, strata=G, host_only=True) as g:
+        g.load_ratings(rng.integers(0, N, n), rng.integers(0, M, n), np.ones(n))
+        assert (g.export_index(ps_mf.IDX_SEQ_LISTS).size > 0) == lists
