@@ -2988,24 +2988,25 @@ int load_ratings(ps_mf_t *h, const int32_t *user, const int32_t *item, const flo
         (r = upload_padded(h, &d.val, L.val, 8)))
       return undo(r);
     if (seq) {
-      const psmf::SeqSet &S = L.seq;
+      psmf::SeqSet &S = h->layout[b].seq;
       DeviceSeq &q = d.seq;
-      q.epoch_chain = S.epoch_chain;
-      std::vector<int32_t> rec;
       if (S.list_beg.empty()) {
-        rec.resize(S.user.size() * 4);
+        q.epoch_chain = S.epoch_chain;
+        std::vector<int32_t> rec(S.user.size() * 4);
         for (size_t x = 0; x < S.user.size(); ++x) {
           rec[4 * x] = S.user[x];
           rec[4 * x + 1] = S.item[x];
           std::memcpy(&rec[4 * x + 2], &S.val[x], sizeof(float));
           rec[4 * x + 3] = S.flag[x];
         }
+        if ((r = upload(h, &q.chain_beg, S.chain_beg)) || (r = upload(h, &q.chain_worker, S.chain_worker)) ||
+            (r = upload(h, &q.rec, rec)))
+          return undo(r);
+      } else {
+        if ((r = upload(h, &q.list_beg, S.list_beg)) || (r = upload(h, &q.rec, S.list_rec))) return undo(r);
+        std::vector<int32_t>().swap(S.list_rec);  // no export reads it
       }
-      if (!S.list_beg.empty() && (r = upload(h, &q.list_beg, S.list_beg))) return undo(r);
-      if ((r = upload(h, &q.chain_beg, S.chain_beg)) || (r = upload(h, &q.chain_worker, S.chain_worker)) ||
-          (r = upload(h, &q.rec, S.list_beg.empty() ? rec : S.list_rec)) || (r = upload(h, &q.item_wptr, S.item_wptr)) ||
-          (r = upload(h, &q.item_workers, S.item_workers)))
-        return undo(r);
+      if ((r = upload(h, &q.item_wptr, S.item_wptr)) || (r = upload(h, &q.item_workers, S.item_workers))) return undo(r);
     } else if ((r = upload_units(h, d.by_user, L.by_user)) || (r = upload_units(h, d.by_item, L.by_item)) ||
                (r = upload(h, &d.by_user.sole, L.by_user.sole)) ||
                (r = upload_cells(h, d.cells_user, L.cells_user)) || (r = upload_cells(h, d.cells_item, L.cells_item)) ||

@@ -82,3 +82,27 @@ def test_long_chains_match_the_oracle_with_and_without_graphs():
     assert np.isfinite(Lo).all() and max(np.abs(L - Lo).max(), np.abs(R - Ro).max()) <= TOL
     Le, Re = by_hand(*args, lists=0, graphs=False)
     assert np.array_equal(L, Le) and np.array_equal(R, Re)
+
+
+def test_lists_keep_no_second_copy_of_the_ratings_on_the_host():
+    """A handle in lists holds as much host memory as one in chains: its records (16 bytes a
+    rating, 48 MB here) are freed once they are on the device; 4 bytes a rating of slack."""
+    from paper_1410_8043_amd import ps_mf
+
+    def resident():
+        with open("/proc/self/statm") as f:
+            return int(f.read().split()[1]) * 4096
+
+    N, M, n = 30_000, 1000, 3_000_000
+    rng = np.random.default_rng(3)
+    user, item = rng.integers(0, N, n).astype(np.int32), rng.integers(0, M, n).astype(np.int32)
+    val = np.ones(n, np.float32)
+    kept = []
+    for lists in (0, 1, 0, 1):  # the first pair warms the allocators up
+        g = ps_mf.PsMf(N, M, 8, 64, 0, 0.01, 0.05, step=ps_mf.STEP_SEQ, seq_lists=lists)
+        before = resident()
+        g.load_ratings(user, item, val)
+        kept.append(resident() - before)
+        g.close()
+    print(f"host bytes kept: {kept}", flush=True)
+    assert kept[3] <= kept[2] + 4 * n, kept
