@@ -1332,7 +1332,9 @@ __global__ __launch_bounds__(kBlock) void k_vap_norms(VapArgs a) {
   }
   // The workgroups tell each other nothing but the norms, by device-wide atomics of this first
   // wavefront: once those are complete it may count the workgroup in.  (A release fence would
-  // write back the whole L2, once per workgroup: 25 us a launch.)
+  // write back the whole L2, once per workgroup: 25 us a launch.)  The wait orders no plain store:
+  // one that the picking workgroup has to see needs that fence, or has to be an atomic of this
+  // wavefront too.  The pick reads after its add has returned, since it depends on the count.
   if (threadIdx.x < 64) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (threadIdx.x == 0 && atomicAdd(a.arrived, 1u) == gridDim.x - 1) {
