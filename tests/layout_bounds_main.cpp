@@ -125,6 +125,8 @@ int main() {
   bad += run("one rating row", tiny, 1, 1, 1, 16, 1, 1, 1, 1, 1, 0);
   bad += run("one rating row seq", tiny, 1, 1, 2, 16, 0, 0, 0, 1, 1, 3, 0);
   bad += run("one rating row seq lists", tiny, 1, 1, 2, 16, 0, 0, 0, 1, 1, 3, 1);
+  bad += run("automatic units", skew, 4, 2, 3, 16, 1 << 30, 0, 0, 0, 64, 0);
+  bad += run("automatic units, no rating", empty, 3, 2, 1, 16, 1 << 30, 0, 0, 0, 8, 0);
   bad += run("empty", empty, 3, 2, 2, 16, 1, 1, 1, 8, 8, 0);
   bad += run("empty seq", empty, 3, 2, 2, 16, 0, 0, 0, 8, 8, 4);
   std::printf("%d failures\n", bad);

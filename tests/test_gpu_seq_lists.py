@@ -61,6 +61,8 @@ def by_oracle(w, N, M, K, P, s, B, G, policy, clocks):
     (150, 200, 2000, 300, 4, 1, 2, 32, oracle.SSP_WORST, True, True),
     (20, 400, 1500, 128, 37, 3, 1, 256, oracle.ESSP_ROW, True, False),
     (1000, 40, 6000, 16, 4, 2, 1, 1, oracle.SSP_LAZY, False, True),
+    (100, 60, 1500, 512, 3, 2, 2, 16, oracle.SSP_ROW, True, True),
+    (60, 300, 2500, 20, 64, 1, 1, 1, oracle.ESSP_ROW, True, True),
 ])
 def test_lists_and_chains_match_the_oracle(N, M, nnz, K, P, s, B, G, policy, hot_user, hot_item):
     print(f"lists: N={N} M={M} nnz={nnz} K={K} P={P} s={s} B={B} G={G} policy={policy}", flush=True)
